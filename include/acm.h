@@ -86,8 +86,13 @@ typedef struct acm_config {
     int32_t graph_chunk;    /* steps per captured HIP graph (even); 0 = 64    */
     int32_t tile;           /* kernel tile variant; 0 = default.  2D single-
                                phase: 1 32x8, 2 64x8, 3 16x16, 4 128x4,
-                               5 32x16 (0: 64x4).  2D axisymmetric: 1
-                               32x8, 2 64x8, 4 64x4 (0: 32x16).  2D two-phase: 1 32x8,
+                               5 32x16 (0: register march along y, up to
+                               three steps per launch inside acm_run, each
+                               run ending with a one-step launch; 64x4 for
+                               rho0 other than 1 and fields of 2 GiB and
+                               more).  2D axisymmetric: 1 32x8, 2 64x8, 4
+                               64x4 (0: register march, else 32x16).  2D
+                               two-phase: 1 32x8,
                                2 64x8, 3 16x16 (0: 32x16).  3D: low byte
                                1 32x8, 2 64x8, 3 32x4, 4 64x4, 5 64x16,
                                7 32x16, 9 128x4, 12 128x8, 13 64x8 with two
@@ -191,9 +196,9 @@ acm_status acm_init(const acm_config* cfg, const acm_fields* a, const acm_fields
 acm_status acm_step(acm_handle* h);
 
 /* nsteps steps, launched as captured HIP graphs of graph_chunk steps plus
- * single launches for the remainder (tile codes 14 and 15: two steps per
- * launch, the last step of the run on its own, so the other set always
- * holds the state one step back).  Async. */
+ * single launches for the remainder (2D default tile and tile codes 14 and
+ * 15: several steps per launch, the last step of the run on its own, so the
+ * other set always holds the state one step back).  Async. */
 acm_status acm_run(acm_handle* h, int64_t nsteps);
 
 /* Diagnostics of the newest state (dumax compares with the other set, so it

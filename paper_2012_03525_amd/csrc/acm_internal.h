@@ -159,6 +159,20 @@ hipError_t launch_step2d(const Coef<T>& c, const State<T>& in, const State<T>& o
 template <typename T>
 hipError_t launch_step3d(const Coef<T>& c, const State<T>& in, const State<T>& out, int tile,
                          hipStream_t s);
+// 2D steps as a register march (kern_march2d.hip): lv steps in one launch,
+// planar or axisymmetric.  A plan with vx = 0: the configuration does not
+// allow it (rho0 other than 1, fields of 2 GiB and more).
+struct March2d {
+    int vx, lv, rows;  // nodes per lane, steps per launch, rows per chunk
+    double us;         // modelled time per step
+};
+template <typename T>
+March2d march2d_plan(const Coef<T>& c, bool axi, int lv);
+template <typename T>
+March2d march2d_multi_plan(const Coef<T>& c, bool axi);  // the lv with the least time per step
+template <typename T>
+hipError_t launch_march2d(const Coef<T>& c, const State<T>& in, const State<T>& out, bool axi, const March2d& p,
+                          hipStream_t s);
 // Two 3D steps in one launch (in -> out holds level n+2) on fully periodic
 // boxes with rho0 = 1 and fields below 2 GiB, selected by tile codes 14 and
 // 15; step3d_pair_ok says whether the configuration and tile code allow it

@@ -231,6 +231,9 @@ struct acm_handle {
     // per launch
     bool pair = false;
     hipGraphExec_t exec_pair[2] = {nullptr, nullptr};
+    // 2D single-phase, default tile: launch shapes of a single step and of a
+    // run's steps (register march; vx = 0 where it does not apply)
+    March2d one{0, 1, 0, 0.0}, multi{0, 1, 0, 0.0};
     // carved from the caller's scratch buffer (acm_scratch_bytes)
     double* partials = nullptr;
     double* result = nullptr;
@@ -260,6 +263,7 @@ hipError_t launch_typed(const acm_handle* h, const Coef<T>& c, int from, hipStre
     if (h->cfg.two_phase && h->cfg.axisym) return launch_twophase_axisym2d<T>(c, in, out, h->cfg.tile, s);
     if (h->cfg.two_phase) return launch_twophase2d<T>(c, in, out, h->cfg.tile, s);
     if (h->cfg.dim == 3) return launch_step3d<T>(c, in, out, h->cfg.tile, s);
+    if (h->one.vx) return launch_march2d<T>(c, in, out, h->cfg.axisym != 0, h->one, s);
     if (h->cfg.axisym) return launch_axisym2d<T>(c, in, out, h->cfg.tile, s);
     return launch_step2d<T>(c, in, out, h->cfg.tile, s);
 }
@@ -268,6 +272,41 @@ hipError_t launch_one(const acm_handle* h, int from, hipStream_t s)
 {
     if (h->cfg.precision == ACM_F64) return launch_typed<double>(h, h->cd, from, s);
     return launch_typed<float>(h, h->cf, from, s);
+}
+
+// the steps of one h->multi launch (2D) from set `from` into the other set
+hipError_t launch_multi(const acm_handle* h, int from, hipStream_t s)
+{
+    const bool axi = h->cfg.axisym != 0;
+    if (h->cfg.precision == ACM_F64)
+        return launch_march2d<double>(h->cd, state_of<double>(h->set[from]), state_of<double>(h->set[1 - from]), axi,
+                                      h->multi, s);
+    return launch_march2d<float>(h->cf, state_of<float>(h->set[from]), state_of<float>(h->set[1 - from]), axi,
+                                 h->multi, s);
+}
+
+// How many multi-step launches nsteps steps begin with; single steps follow.  The last step is a single one, so the other set then holds the
+// state one step back, and every launch flips the sets: with two steps per
+// launch their count is kept even, so that the newest state lies in the set
+// it would lie in after single steps (three steps per launch flip like three
+// single steps do).
+int64_t multi_launches(const acm_handle* h, int64_t nsteps)
+{
+    if (h->multi.lv < 2 || nsteps < 2) return 0;
+    const int64_t n = (nsteps - 1) / h->multi.lv;
+    return h->multi.lv % 2 ? n : n - n % 2;
+}
+
+// nsteps steps from set `from` on stream s, launch by launch
+hipError_t launch_steps(const acm_handle* h, int from, int64_t nsteps, hipStream_t s)
+{
+    const int64_t m = multi_launches(h, nsteps), n = nsteps - m * (h->multi.lv - 1);
+    for (int64_t i = 0; i < n; ++i) {
+        const int f = (int)((from + i) & 1);
+        const hipError_t e = i < m ? launch_multi(h, f, s) : launch_one(h, f, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // two steps from set `from` into the other set
@@ -286,15 +325,15 @@ acm_status build_graph(acm_handle* h, int parity, bool pair)
 {
     hipError_t e = hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-    const int nl = pair ? h->chunk / 2 : h->chunk;
-    for (int i = 0; i < nl; ++i) {
-        e = pair ? launch_pair(h, (parity + i) & 1, h->cap) : launch_one(h, (parity + i) & 1, h->cap);
-        if (e != hipSuccess) {
-            hipGraph_t g = nullptr;
-            (void)hipStreamEndCapture(h->cap, &g);
-            if (g) (void)hipGraphDestroy(g);
-            return hip_fail(e, "kernel launch during capture");
-        }
+    if (pair)
+        for (int i = 0; i < h->chunk / 2 && e == hipSuccess; ++i) e = launch_pair(h, (parity + i) & 1, h->cap);
+    else
+        e = launch_steps(h, parity, h->chunk, h->cap);
+    if (e != hipSuccess) {
+        hipGraph_t g = nullptr;
+        (void)hipStreamEndCapture(h->cap, &g);
+        if (g) (void)hipGraphDestroy(g);
+        return hip_fail(e, "kernel launch during capture");
     }
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(h->cap, &g);
@@ -388,6 +427,11 @@ acm_status acm_init(const acm_config* cfg, const acm_fields* a, const acm_fields
     if (cfg->dim == 3 && !cfg->two_phase)
         h->pair = cfg->precision == ACM_F64 ? step3d_pair_ok<double>(h->cd, cfg->tile)
                                             : step3d_pair_ok<float>(h->cf, cfg->tile);
+    if (cfg->dim == 2 && !cfg->two_phase && cfg->tile == 0) {
+        const bool axi = cfg->axisym != 0, f64 = cfg->precision == ACM_F64;
+        h->one = f64 ? march2d_plan<double>(h->cd, axi, 1) : march2d_plan<float>(h->cf, axi, 1);
+        h->multi = f64 ? march2d_multi_plan<double>(h->cd, axi) : march2d_multi_plan<float>(h->cf, axi);
+    }
     hipError_t e = hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking);
     if (e != hipSuccess) {
         delete h;
@@ -446,9 +490,11 @@ acm_status acm_run(acm_handle* h, int64_t nsteps)
         h->step += h->chunk;  // chunk is even: the parity is unchanged
         nsteps -= h->chunk;
     }
-    for (int64_t i = 0; i < nsteps; ++i) {
-        acm_status st = acm_step(h);
-        if (st != ACM_OK) return st;
+    if (nsteps > 0) {
+        hipError_t e = launch_steps(h, h->which, nsteps, h->stream);
+        if (e != hipSuccess) return hip_fail(e, "step launch");
+        h->which ^= (int)(nsteps & 1);
+        h->step += nsteps;
     }
     return ACM_OK;
 }

@@ -22,7 +22,7 @@ __device__ __forceinline__ T axi_div_r(T g, T irc, T diff_ns, T sum_cn)
 template <typename T>
 __device__ __forceinline__ T axi_lap_r(T g, T irc, T fC, T fN, T fS)
 {
-    return fmaT(g, (fN + fS) - T(2) * fC, fN - fC) * irc;
+    return fmaT(g, fmaT(T(-2), fC, fN + fS), fN - fC) * irc;  // 2 fC is exact
 }
 
 // Continuity (2.10) sums of the axisymmetric step: the divergence of m (in
@@ -33,7 +33,7 @@ __device__ __forceinline__ void axi_continuity(T rho0, T g, T irc, T rC, T rE, T
 {
     const T myC = fmaT(rC, vC, rho0 * vC), myN = fmaT(rN, vN, rho0 * vN);
     div = mdiff(rE, uE, rW, uW, rho0) + axi_div_r(g, irc, mdiff(rN, vN, rS, vS, rho0), myC + myN);
-    lap = ((rE + rW) - T(2) * rC) + axi_lap_r(g, irc, rC, rN, rS);
+    lap = fmaT(T(-2), rC, rE + rW) + axi_lap_r(g, irc, rC, rN, rS);
 }
 
 // Momentum (2.11) sums of the axisymmetric step at a node: fluxes of Pi
@@ -49,8 +49,8 @@ __device__ __forceinline__ void axi_momentum(T cs2, T g, T irc, T rC, T rE, T rW
     const T pyyC = fmaT(myC, vC, cs2 * rC), pyyN = fmaT(myN, vN, cs2 * rN), pyyS = fmaT(myS, vS, cs2 * rS);
     fxx = (fmaT(mxE, uE, cs2 * rE) - fmaT(mxW, uW, cs2 * rW)) + axi_div_r(g, irc, pxyN - pxyS, pxyC + pxyN);
     fyy = (myE * uE - myW * uW) + axi_div_r(g, irc, pyyN - pyyS, pyyC + pyyN) - T(2) * cs2 * rC * irc;
-    lpx = ((mxE + mxW) - T(2) * mxC) + axi_lap_r(g, irc, mxC, mxN, mxS);
-    lpy = ((myE + myW) - T(2) * myC) + axi_lap_r(g, irc, myC, myN, myS) - myC * irc * irc;
+    lpx = fmaT(T(-2), mxC, mxE + mxW) + axi_lap_r(g, irc, mxC, mxN, mxS);
+    lpy = fmaT(T(-2), myC, myE + myW) + axi_lap_r(g, irc, myC, myN, myS) - myC * irc * irc;
 }
 
 // One axisymmetric single-phase step (x axial, y radial, axis on the -y
