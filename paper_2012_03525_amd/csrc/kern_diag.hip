@@ -20,6 +20,16 @@ namespace acm {
 
 __device__ __forceinline__ bool is_max_slot(int q) { return q == 5 || q == 6 || q == 9 || q == 11; }
 
+// sum (or maximum) of 256 values by one wave, strides 128, 64, then 32 .. 1
+__device__ __forceinline__ double tree256(const double* v, int lane, bool mx)
+{
+    auto op = [mx](double a, double b) { return mx ? fmax(a, b) : a + b; };
+    double x = op(op(v[lane], v[lane + 128]), op(v[lane + 64], v[lane + 192]));
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) x = op(x, __shfl_down(x, s));
+    return x;
+}
+
 template <typename T>
 __device__ __forceinline__ void load_vel(const Coef<T>& c, int dim, const State<T>& s, int gx, int gy, int gz,
                                          double& u, double& v, double& w)
@@ -113,43 +123,37 @@ __global__ __launch_bounds__(256) void diag_partial_kernel(Coef<T> c, int dim, i
         const double chk = r + u + v + w + ph;
         if (!isfinite(chk)) acc[11] = 1.0;
     }
-    // block tree reduction (fixed order)
-    __shared__ double red[256];
-    for (int q = 0; q < NDIAG; ++q) {
-        red[threadIdx.x] = acc[q];
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) {
-                const double a = red[threadIdx.x], b = red[threadIdx.x + s];
-                red[threadIdx.x] = is_max_slot(q) ? fmax(a, b) : a + b;
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) partials[(size_t)blockIdx.x * NDIAG + q] = red[0];
-        __syncthreads();
+    // Block reduction in a fixed order: the tree of strides 128, 64, ..., 1.
+    // All quantities are laid out at once and each wave reduces every fourth
+    // one, the last six strides by lane shuffles: one barrier instead of nine
+    // per quantity (256^2: 18.3 -> 7.7 us).
+    __shared__ double red[NDIAG][256];
+#pragma unroll
+    for (int q = 0; q < NDIAG; ++q) red[q][threadIdx.x] = acc[q];
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    for (int q = threadIdx.x >> 6; q < NDIAG; q += 4) {
+        const double v = tree256(red[q], lane, is_max_slot(q));
+        if (lane == 0) partials[(size_t)blockIdx.x * NDIAG + q] = v;
     }
 }
 
+// One workgroup per quantity (one workgroup for all of them in turn took
+// 17.5 us at 256 partials, 5.4 now).
 __global__ __launch_bounds__(256) void diag_final_kernel(const double* partials, int nblocks, double* result)
 {
     __shared__ double red[256];
-    for (int q = 0; q < NDIAG; ++q) {
-        double a = 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += 256) {
-            const double x = partials[(size_t)b * NDIAG + q];
-            a = is_max_slot(q) ? fmax(a, x) : a + x;
-        }
-        red[threadIdx.x] = a;
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) {
-                const double x = red[threadIdx.x], y = red[threadIdx.x + s];
-                red[threadIdx.x] = is_max_slot(q) ? fmax(x, y) : x + y;
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) result[q] = red[0];
-        __syncthreads();
+    const int q = blockIdx.x;
+    double a = 0.0;
+    for (int b = threadIdx.x; b < nblocks; b += 256) {
+        const double x = partials[(size_t)b * NDIAG + q];
+        a = is_max_slot(q) ? fmax(a, x) : a + x;
+    }
+    red[threadIdx.x] = a;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const double v = tree256(red, threadIdx.x, is_max_slot(q));
+        if (threadIdx.x == 0) result[q] = v;
     }
 }
 
@@ -161,7 +165,7 @@ hipError_t launch_diag_impl(const Coef<T>& c, int dim, int two_phase, const Stat
                        have_prev, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(256), 0, s, partials, nblocks, result);
+    hipLaunchKernelGGL(diag_final_kernel, dim3(NDIAG), dim3(256), 0, s, partials, nblocks, result);
     return hipGetLastError();
 }
 
