@@ -434,6 +434,39 @@ acm_status acm_cnn_adam(int64_t n, float* p, const float* g, float* m, float* v,
 
 acm_status acm_cnn_to_bf16(size_t n, const float* src, void* dst, void* stream);
 
+/* The whole network as training holds it: per layer the fp32 parameters, their
+ * gradients and Adam moments, the bf16 weights and their transposed copies
+ * (acm_cnn_transpose), the bf16 input activations and, for layers 1..4, the
+ * bf16 gradient with respect to the pre-activation that produced acts[l]
+ * (gacts[l - 1]); raw: the fp32 output (16 channels); workspace: the largest
+ * acm_cnn_wgrad_workspace of the layers.  All device memory of the caller. */
+typedef struct acm_cnn_net {
+    float *w32[ACM_CNN_LAYERS], *b32[ACM_CNN_LAYERS];
+    float *gw[ACM_CNN_LAYERS], *gb[ACM_CNN_LAYERS];
+    float *mw[ACM_CNN_LAYERS], *vw[ACM_CNN_LAYERS], *mb[ACM_CNN_LAYERS], *vb[ACM_CNN_LAYERS];
+    void *w16[ACM_CNN_LAYERS], *wt16[ACM_CNN_LAYERS];
+    void *acts[ACM_CNN_LAYERS], *gacts[ACM_CNN_LAYERS];
+    float *raw, *workspace;
+} acm_cnn_net;
+
+/* raw = f(in_scale * q): acm_cnn_pack into acts[0], then the five layers
+ * (acm_cnn_conv), every layer's input kept in acts.  With out: instead of
+ * raw, the corrected state out[c] = q[c] + out_scale[c] * raw[c] (bit for bit
+ * acm_cnn_apply on a copy of q; out must not alias q). */
+acm_status acm_cnn_net_forward(int32_t nx, int32_t ny, const acm_cnn_net* net, const acm_fields* q,
+                               const float* in_scale, const acm_fields* out, const float* out_scale, void* stream);
+
+/* Backward of the acm_cnn_net_forward that filled acts, from gout (bf16, 16 channels, the
+ * gradient with respect to raw): gw and gb of every layer (acm_cnn_wgrad, or
+ * acm_cnn_wgrad_add with accumulate != 0) and, when gin is given, the fp32
+ * gradient with respect to acts[0] (16 channels; zero_bias: 16 fp32 zeros). */
+acm_status acm_cnn_net_backward(int32_t nx, int32_t ny, const acm_cnn_net* net, const void* gout, int32_t accumulate,
+                                float* gin, const float* zero_bias, void* stream);
+
+/* acm_cnn_adam on every parameter (step t >= 1), with the bf16 weights and
+ * their transposed copies brought up to date, in one launch. */
+acm_status acm_cnn_net_adam(const acm_cnn_net* net, float lr, float b1, float b2, float eps, int64_t t, void* stream);
+
 /* Coarse (I, J) = mean of fine nodes (fI..fI+f-1, fJ..fJ+f-1) for drho, u, v. */
 acm_status acm_filter_box(int32_t nxf, int32_t nyf, int32_t factor, int32_t precision, const acm_fields* fine,
                           const acm_fields* coarse, void* stream);

@@ -69,6 +69,12 @@ class BatchCaseStatus(ctypes.Structure):
                 ("done_ms", ctypes.c_double), ("umax", ctypes.c_double)]
 
 
+class CnnNet(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p * 5) for n in ("w32", "b32", "gw", "gb", "mw", "vw", "mb", "vb", "w16", "wt16",
+                                                   "acts", "gacts")] + [("raw", ctypes.c_void_p),
+                                                                        ("workspace", ctypes.c_void_p)]
+
+
 _lib: Optional[ctypes.CDLL] = None
 
 # exported symbols and their ctypes signatures (also checked by the CPU tests)
@@ -136,6 +142,13 @@ SIGNATURES = {
                                            ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
     "acm_cnn_adam": (ctypes.c_int, [ctypes.c_int64] + [ctypes.c_void_p] * 5 + [ctypes.c_float] * 4 +
                      [ctypes.c_int64, ctypes.c_void_p]),
+    "acm_cnn_net_forward": (ctypes.c_int, [ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(CnnNet),
+                                           ctypes.POINTER(Fields), ctypes.POINTER(ctypes.c_float),
+                                           ctypes.POINTER(Fields), ctypes.POINTER(ctypes.c_float), ctypes.c_void_p]),
+    "acm_cnn_net_backward": (ctypes.c_int, [ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(CnnNet), ctypes.c_void_p,
+                                            ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
+    "acm_cnn_net_adam": (ctypes.c_int, [ctypes.POINTER(CnnNet)] + [ctypes.c_float] * 4 +
+                         [ctypes.c_int64, ctypes.c_void_p]),
     "acm_cnn_to_bf16": (ctypes.c_int, [ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
     "acm_filter_box": (ctypes.c_int, [ctypes.c_int32] * 4 + [ctypes.POINTER(Fields), ctypes.POINTER(Fields),
                                                              ctypes.c_void_p]),

@@ -89,6 +89,7 @@ class Network:
         self.loss_ws = torch.zeros(acm.lib().acm_cnn_loss_workspace(nx, ny) // 8 + 1, dtype=torch.float64,
                                    device=self.dev)
         self.loss_buf = torch.zeros(1, dtype=torch.float64, device=self.dev)
+        self._net = acm.CnnNet()
         self.t = 0
         self.load(params if params is not None else he_init(seed))
 
@@ -125,17 +126,39 @@ class Network:
         for l, (ci, co) in enumerate(self.shapes):
             acm.check(L.acm_cnn_transpose(ci, co, _vp(self.w16[l]), _vp(self.wt16[l]), self.stream))
 
+    def _layers(self, *names, acts=None):
+        """The argument block of the whole-network calls with these tensors'
+        pointers (taken anew for every call) and the given activations."""
+        for name in names:
+            field = getattr(self._net, name)
+            for l, t in enumerate(getattr(self, name)):
+                field[l] = t.data_ptr()
+        for l, t in enumerate(acts if acts is not None else self.acts):
+            self._net.acts[l] = t.data_ptr()
+        return self._net
+
+    def new_acts(self):
+        """One more set of activation buffers (for forward and backward)."""
+        return [self.torch.zeros_like(a) for a in self.acts]
+
     # -- forward / backward ---------------------------------------------------
-    def forward(self, drho, u, v):
-        """raw = f(N q) for the state tensors (ny, nx) fp32."""
-        L = acm.lib()
-        acm.check(L.acm_cnn_pack(self.nx, self.ny, _vp(drho), _vp(u), _vp(v), _f3(self.in_scale),
-                                 _vp(self.acts[0]), self.stream))
-        for l, (ci, co) in enumerate(self.shapes):
-            last = l == LAYERS - 1
-            y = self.raw if last else self.acts[l + 1]
-            acm.check(L.acm_cnn_conv(self.nx, self.ny, ci, co, CONV_RAW if last else CONV_RELU, _vp(self.acts[l]),
-                                     _vp(self.w16[l]), _vp(self.b32[l]), None, _vp(y), self.stream))
+    def forward(self, drho, u, v, out=None, acts=None):
+        """raw = f(N q) for the state tensors (ny, nx) fp32, or with out (a
+        state dict) the corrected state q + D f(N q) instead."""
+        net = self._layers("w16", "b32", acts=acts)
+        net.raw = self.raw.data_ptr()
+        q = acm.Fields(drho.data_ptr(), u.data_ptr(), v.data_ptr(), None, None)
+        acm.check(acm.lib().acm_cnn_net_forward(self.nx, self.ny, net, q, _f3(self.in_scale),
+                                                None if out is None else _fields(out), _f3(self.out_scale),
+                                                self.stream))
+
+    def backward(self, accumulate: bool = False, gin=None, zero16=None, acts=None):
+        """Gradients of all parameters (into gw, gb; added with accumulate)
+        from gout, and the input gradient into gin if given."""
+        net = self._layers("wt16", "gw", "gb", "gacts", acts=acts)
+        net.workspace = self.wg_ws.data_ptr()
+        acm.check(acm.lib().acm_cnn_net_backward(self.nx, self.ny, net, _vp(self.gout), int(accumulate), _vp(gin),
+                                                 _vp(zero16), self.stream))
 
     def correct(self, src: Dict[str, "object"], dst: Dict[str, "object"]):
         """dst = src + D f(N src) in one fused launch (nx, ny multiples of 16)."""
@@ -157,27 +180,13 @@ class Network:
         t = (ctypes.c_void_p * 3)(*[target[k].data_ptr() for k in ("drho", "u", "v")])
         acm.check(L.acm_cnn_loss(self.nx, self.ny, _vp(self.raw), b, t, _f3(self.out_scale), _vp(self.gout),
                                  _vp(self.loss_ws), _vp(self.loss_buf), self.stream))
-        g = self.gout
-        for l in range(LAYERS - 1, -1, -1):
-            ci, co = self.shapes[l]
-            acm.check(L.acm_cnn_wgrad(self.nx, self.ny, ci, co, _vp(self.acts[l]), _vp(g), _vp(self.wg_ws),
-                                      _vp(self.gw[l]), _vp(self.gb[l]), self.stream))
-            if l > 0:
-                gx = self.gacts[l - 1]  # gradient w.r.t. the pre-activation producing acts[l]
-                acm.check(L.acm_cnn_conv(self.nx, self.ny, co, ci, CONV_MASK, _vp(g), _vp(self.wt16[l]), None,
-                                         _vp(self.acts[l]), _vp(gx), self.stream))
-                g = gx
+        self.backward()
         return self.loss_buf
 
     def adam(self, lr: float, b1: float = 0.9, b2: float = 0.999, eps: float = 1e-8):
-        L = acm.lib()
         self.t += 1
-        for l in range(LAYERS):
-            acm.check(L.acm_cnn_adam(self.w32[l].numel(), _vp(self.w32[l]), _vp(self.gw[l]), _vp(self.mw[l]),
-                                     _vp(self.vw[l]), _vp(self.w16[l]), lr, b1, b2, eps, self.t, self.stream))
-            acm.check(L.acm_cnn_adam(self.b32[l].numel(), _vp(self.b32[l]), _vp(self.gb[l]), _vp(self.mb[l]),
-                                     _vp(self.vb[l]), None, lr, b1, b2, eps, self.t, self.stream))
-        self.refresh_transposed()
+        net = self._layers("w32", "b32", "gw", "gb", "mw", "vw", "mb", "vb", "w16", "wt16")
+        acm.check(acm.lib().acm_cnn_net_adam(net, lr, b1, b2, eps, self.t, self.stream))
 
     def train_step(self, base, target, lr: float):
         self.forward(base["drho"], base["u"], base["v"])
@@ -382,8 +391,8 @@ class Unroll:
     pass runs, for j = k .. 1, the state loss of step j, the network
     backward (weight gradients summed over the steps, and the gradient with
     respect to the network input) and the adjoint of the SMAME step, all in
-    libacm; the network activations of each step are recomputed from the
-    stored uncorrected state."""
+    libacm; the network activations of every step are kept for it (19 MB a
+    step at 256^2)."""
 
     def __init__(self, spec: FlowSpec, net: Network, k: int, div_beta: float = 0.0):
         import torch
@@ -404,30 +413,29 @@ class Unroll:
         self.zero16 = torch.zeros(16, dtype=torch.float32, device=dev)
         self.loss = torch.zeros(1, dtype=torch.float64, device=dev)
         self.loss_dummy = torch.zeros(1, dtype=torch.float64, device=dev)
-        self.solver = acm.Solver(spec.coarse_config(), None, tensors=[state(), state()],
-                                 force_x=spec.coarse_force())
+        self.acts = [None] + [net.acts if j == k else net.new_acts() for j in range(1, k + 1)]
+        # one handle per step, from q_{j-1} into s_j, so that nothing is copied
+        # (single steps only: graphs of two steps; the first checks stability)
+        self.solvers = []
+        for j in range(1, k + 1):
+            cfg = spec.coarse_config()
+            cfg.graph_chunk, cfg.allow_unstable = 2, int(j > 1)
+            self.solvers.append(acm.Solver(cfg, None, tensors=[self.q[j - 1], self.s[j]],
+                                           force_x=spec.coarse_force()))
+        self.solver = self.solvers[0]
 
     def close(self):
-        self.solver.close()
-
-    def _step(self, src, dst):
-        for kk in src:
-            self.solver.sets[0][kk].copy_(src[kk])
-        self.solver.set_current(0, 0)
-        self.solver.step()
-        for kk in dst:
-            dst[kk].copy_(self.solver.sets[1][kk])
+        for s in self.solvers:
+            s.close()
 
     def forward(self, q0):
-        net = self.net
-        for kk in q0:
-            self.q[0][kk].copy_(q0[kk])
+        """q_0 .. q_k; the activations of every step are kept."""
+        self.torch._foreach_copy_([self.q[0][kk] for kk in q0], [q0[kk] for kk in q0])
         for j in range(1, self.k + 1):
-            self._step(self.q[j - 1], self.s[j])
-            net.forward(self.s[j]["drho"], self.s[j]["u"], self.s[j]["v"])
-            for kk in self.s[j]:
-                self.q[j][kk].copy_(self.s[j][kk])
-            net.apply(self.q[j]["drho"], self.q[j]["u"], self.q[j]["v"])
+            self.solvers[j - 1].set_current(0, 0)
+            self.solvers[j - 1].step()
+            s = self.s[j]
+            self.net.forward(s["drho"], s["u"], s["v"], out=self.q[j], acts=self.acts[j])
 
     def loss_and_grads(self, q0, targets, adj_q0: bool = False):
         """Loss of the window and its gradients in net.gw / net.gb (and, with
@@ -437,11 +445,8 @@ class Unroll:
         assert len(targets) == k
         nx, ny = net.nx, net.ny
         self.forward(q0)
-        self.loss.zero_()
         lam, lam_next = self.lam
-        for kk in lam:
-            lam[kk].zero_()
-        first = True
+        self.torch._foreach_zero_([self.loss] + list(lam.values()))
         for j in range(k, 0, -1):
             qj = (ctypes.c_void_p * 3)(*[self.q[j][kk].data_ptr() for kk in ("drho", "u", "v")])
             tj = (ctypes.c_void_p * 3)(*[targets[j - 1][kk].data_ptr() for kk in ("drho", "u", "v")])
@@ -456,34 +461,22 @@ class Unroll:
                 acm.check(L.acm_cnn_div_penalty(nx, ny, qv, sv, self.div_weight / k, av, None, _vp(net.loss_ws),
                                                 _vp(self.loss), net.stream))
             # lam = dL/dq_j; the correction adds D raw, so dL/draw = D lam
-            net.forward(sj["drho"], sj["u"], sj["v"])
             acm.check(L.acm_cnn_pack(nx, ny, _vp(lam["drho"]), _vp(lam["u"]), _vp(lam["v"]), _f3(net.out_scale),
                                      _vp(net.gout), net.stream))
-            g = net.gout
-            wg = L.acm_cnn_wgrad if first else L.acm_cnn_wgrad_add
-            for l in range(LAYERS - 1, -1, -1):
-                ci, co = net.shapes[l]
-                acm.check(wg(nx, ny, ci, co, _vp(net.acts[l]), _vp(g), _vp(net.wg_ws), _vp(net.gw[l]),
-                             _vp(net.gb[l]), net.stream))
-                if l > 0:
-                    gx = net.gacts[l - 1]
-                    acm.check(L.acm_cnn_conv(nx, ny, co, ci, CONV_MASK, _vp(g), _vp(net.wt16[l]), None,
-                                             _vp(net.acts[l]), _vp(gx), net.stream))
-                    g = gx
-            first = False
-            # gradient with respect to the network input, then through N
-            ci0, co0 = net.shapes[0]
-            acm.check(L.acm_cnn_conv(nx, ny, co0, ci0, CONV_RAW, _vp(g), _vp(net.wt16[0]), _vp(self.zero16), None,
-                                     _vp(self.gin), net.stream))
+            through = j > 1 or adj_q0  # dL/dq_{j-1} is wanted
+            # weight gradients, and the gradient with respect to the network input
+            net.backward(accumulate=j < k, gin=self.gin if through else None, zero16=self.zero16,
+                         acts=self.acts[j])
+            if not through:
+                break
             acm.check(L.acm_cnn_apply(nx, ny, _vp(self.gin), _f3(net.in_scale), _vp(lam["drho"]), _vp(lam["u"]),
                                       _vp(lam["v"]), net.stream))
             if self.div_weight:  # the penalty's own dependence on s_j (div(s - q) = -div(q - s))
                 acm.check(L.acm_cnn_div_penalty(nx, ny, sv, qv, self.div_weight / k, av, None, _vp(net.loss_ws),
                                                 _vp(self.loss_dummy), net.stream))
             # lam = dL/ds_j; through the step to dL/dq_{j-1}
-            if j > 1 or adj_q0:
-                self.solver.adjoint(self.q[j - 1], sj, lam, lam_next)
-                lam, lam_next = lam_next, lam
+            self.solver.adjoint(self.q[j - 1], sj, lam, lam_next)
+            lam, lam_next = lam_next, lam
         self.adj_q0 = lam if adj_q0 else None
         return self.loss
 

@@ -53,7 +53,14 @@ __device__ __forceinline__ float bf2f(bf16_t h) { return __uint_as_float(((unsig
 
 __device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
-enum : int { CONV_RELU = 0, CONV_RAW = 1, CONV_MASK = 2 };
+enum : int { CONV_RELU = 0, CONV_RAW = 1, CONV_MASK = 2, CONV_CORRECT = 3 };
+
+// fields of CONV_CORRECT: out[c] = q[c] + d[c] (conv + b)[c]
+struct Correct {
+    const float* q[3];
+    float* out[3];
+    float d[3];
+};
 
 // ---------------------------------------------------------------------------
 // forward convolution: workgroup tile TR rows x 32 columns, 4 waves; wave w
@@ -65,6 +72,7 @@ enum : int { CONV_RELU = 0, CONV_RAW = 1, CONV_MASK = 2 };
 // MODE: CONV_RELU   y = bf16(relu(conv + b))
 //       CONV_RAW    y = fp32(conv + b)
 //       CONV_MASK   y = bf16(conv * (mask > 0))   (data gradient through ReLU)
+//       CONV_CORRECT  the correction cr of the first three channels, y unused
 // ---------------------------------------------------------------------------
 // Operands of the K = 32 (CIN a multiple of 32) or K = 16 (CIN = 16) product:
 // KW channels per lane, lane group lg holding channels KW lg .. KW lg + KW - 1
@@ -88,7 +96,8 @@ struct ConvK {
 template <int CIN, int COUT, int MODE, int TR = 4>
 __global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const bf16_t* __restrict__ x,
                                                       const bf16_t* __restrict__ w, const float* __restrict__ bias,
-                                                      const bf16_t* __restrict__ mask, void* __restrict__ y)
+                                                      const bf16_t* __restrict__ mask, void* __restrict__ y,
+                                                      Correct cr)
 {
     using K = ConvK<CIN>;
     using op = typename K::op;
@@ -171,6 +180,14 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const bf16_t
                     static_cast<bf16_t*>(y)[o] = f2bf(val);
                 } else if constexpr (MODE == CONV_RAW) {
                     static_cast<float*>(y)[o] = val + bias[co];
+                } else if constexpr (MODE == CONV_CORRECT) {
+                    if (co < 3) {
+                        const size_t p = (size_t)py * W + px;
+                        const float* q = co == 0 ? cr.q[0] : co == 1 ? cr.q[1] : cr.q[2];
+                        float* out = co == 0 ? cr.out[0] : co == 1 ? cr.out[1] : cr.out[2];
+                        const float d = co == 0 ? cr.d[0] : co == 1 ? cr.d[1] : cr.d[2];
+                        out[p] = fmaf(d, val + bias[co], q[p]);
+                    }
                 } else {
                     const bf16_t m = mask[o];
                     const bool pos = (m & 0x8000u) == 0 && (m & 0x7FFFu) != 0;
@@ -564,13 +581,11 @@ __global__ __launch_bounds__(64) void loss_accumulate_kernel(const double* __res
     if (threadIdx.x == 0) out[0] += t * scale;
 }
 
-// Adam (Kingma & Ba) with bias correction; p16 (optional) receives bf16(p)
-__global__ void adam_kernel(int n, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, bf16_t* __restrict__ p16, float lr, float b1, float b2, float eps,
-                            float c1, float c2)
+// Adam (Kingma & Ba) with bias correction; returns the new parameter
+__device__ __forceinline__ float adam_update(int e, float* __restrict__ p, const float* __restrict__ g,
+                                             float* __restrict__ m, float* __restrict__ v, float lr, float b1,
+                                             float b2, float eps, float c1, float c2)
 {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= n) return;
     const float ge = g[e];
     const float me = fmaf(b1, m[e], (1.f - b1) * ge);
     const float ve = fmaf(b2, v[e], (1.f - b2) * ge * ge);
@@ -578,7 +593,44 @@ __global__ void adam_kernel(int n, float* __restrict__ p, const float* __restric
     v[e] = ve;
     const float pe = p[e] - lr * (me / c1) / (sqrtf(ve / c2) + eps);
     p[e] = pe;
+    return pe;
+}
+
+// p16 (optional) receives bf16(p)
+__global__ void adam_kernel(int n, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
+                            float* __restrict__ v, bf16_t* __restrict__ p16, float lr, float b1, float b2, float eps,
+                            float c1, float c2)
+{
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= n) return;
+    const float pe = adam_update(e, p, g, m, v, lr, b1, b2, eps, c1, c2);
     if (p16) p16[e] = f2bf(pe);
+}
+
+// Adam on every parameter of the network in one launch (ten launches and
+// five transposes otherwise, 2.4 us each): grid y = layer, x over the layer's
+// weights then its biases; the bf16 weights and their transposed copy
+// wt[8 - t][i][o] = w[t][o][i] follow the update.
+struct NetAdam {
+    float *w[ACM_CNN_LAYERS], *b[ACM_CNN_LAYERS], *mw[ACM_CNN_LAYERS], *vw[ACM_CNN_LAYERS], *mb[ACM_CNN_LAYERS],
+        *vb[ACM_CNN_LAYERS];
+    const float *gw[ACM_CNN_LAYERS], *gb[ACM_CNN_LAYERS];
+    bf16_t *w16[ACM_CNN_LAYERS], *wt16[ACM_CNN_LAYERS];
+    int cin[ACM_CNN_LAYERS], cout[ACM_CNN_LAYERS];
+};
+__global__ __launch_bounds__(256) void net_adam_kernel(NetAdam a, float lr, float b1, float b2, float eps, float c1,
+                                                       float c2)
+{
+    const int l = blockIdx.y, ci = a.cin[l], co = a.cout[l], nw = 9 * ci * co;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e < nw) {
+        const bf16_t h = f2bf(adam_update(e, a.w[l], a.gw[l], a.mw[l], a.vw[l], lr, b1, b2, eps, c1, c2));
+        const int t = e / (ci * co), r = e - t * (ci * co), o = r / ci, i = r - o * ci;
+        a.w16[l][e] = h;
+        a.wt16[l][((8 - t) * ci + i) * co + o] = h;
+    } else if (e < nw + co) {
+        adam_update(e - nw, a.b[l], a.gb[l], a.mb[l], a.vb[l], lr, b1, b2, eps, c1, c2);
+    }
 }
 
 __global__ void to_bf16_kernel(size_t n, const float* __restrict__ s, bf16_t* __restrict__ d)
@@ -626,10 +678,10 @@ constexpr int CONV_TR = 4;  // rows per workgroup tile (two workgroups per CU at
 
 template <int CIN, int COUT, int MODE>
 hipError_t launch_conv(int H, int W, const bf16_t* x, const bf16_t* w, const float* b, const bf16_t* mask, void* y,
-                       hipStream_t s)
+                       hipStream_t s, const Correct& cr = Correct{})
 {
     hipLaunchKernelGGL((conv3x3_kernel<CIN, COUT, MODE, CONV_TR>), dim3((W / 32) * (H / CONV_TR)), dim3(256), 0, s, H,
-                       W, x, w, b, mask, y);
+                       W, x, w, b, mask, y, cr);
     return hipGetLastError();
 }
 
@@ -1407,6 +1459,96 @@ acm_status acm_cnn_adam(int64_t n, float* p, const float* g, float* m, float* v,
     const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
     hipLaunchKernelGGL(adam_kernel, dim3(blocks_for((size_t)n)), dim3(256), 0, static_cast<hipStream_t>(stream), (int)n,
                        p, g, m, v, static_cast<bf16_t*>(p16), lr, b1, b2, eps, c1, c2);
+    return chip(hipGetLastError(), "adam launch");
+}
+
+static const int NET_CI[ACM_CNN_LAYERS] = {16, 32, 32, 32, 32};
+static const int NET_CO[ACM_CNN_LAYERS] = {32, 32, 32, 32, 16};
+
+acm_status acm_cnn_net_forward(int32_t nx, int32_t ny, const acm_cnn_net* net, const acm_fields* q,
+                               const float* in_scale, const acm_fields* out, const float* out_scale, void* stream)
+{
+    if (!net || !q || !in_scale || (out ? !out_scale : !net->raw)) return cfail(ACM_EINVAL, "NULL pointer");
+    if (!grid_ok(nx, ny)) return cfail(ACM_EINVAL, "network grids need nx % 64 == 0 and ny % 8 == 0");
+    for (int l = 0; l < ACM_CNN_LAYERS; ++l)
+        if (!net->acts[l] || !net->w16[l] || !net->b32[l]) return cfail(ACM_EINVAL, "NULL layer pointer");
+    const void* const in[3] = {q->drho, q->u, q->v};
+    Correct cr{};
+    if (out) {
+        void* const o[3] = {out->drho, out->u, out->v};
+        for (int c = 0; c < 3; ++c) {
+            for (int k = 0; k < 3; ++k)
+                if (!o[c] || o[c] == in[k]) return cfail(ACM_EINVAL, "out must be given and distinct from q");
+            cr.q[c] = static_cast<const float*>(in[c]);
+            cr.out[c] = static_cast<float*>(o[c]);
+            cr.d[c] = out_scale[c];
+        }
+    }
+    acm_status st = acm_cnn_pack(nx, ny, static_cast<const float*>(in[0]), static_cast<const float*>(in[1]),
+                                 static_cast<const float*>(in[2]), in_scale, net->acts[0], stream);
+    for (int l = 0; l < ACM_CNN_LAYERS - 1 && st == ACM_OK; ++l)
+        st = acm_cnn_conv(nx, ny, NET_CI[l], NET_CO[l], ACM_CONV_RELU, net->acts[l], net->w16[l], net->b32[l], nullptr,
+                          net->acts[l + 1], stream);
+    if (st != ACM_OK) return st;
+    constexpr int L = ACM_CNN_LAYERS - 1;
+    if (!out)
+        return acm_cnn_conv(nx, ny, NET_CI[L], NET_CO[L], ACM_CONV_RAW, net->acts[L], net->w16[L], net->b32[L], nullptr,
+                            net->raw, stream);
+    return chip(launch_conv<32, 16, CONV_CORRECT>(ny, nx, static_cast<const bf16_t*>(net->acts[L]),
+                                                  static_cast<const bf16_t*>(net->w16[L]), net->b32[L], nullptr,
+                                                  nullptr, static_cast<hipStream_t>(stream), cr),
+                "correction launch");
+}
+
+acm_status acm_cnn_net_backward(int32_t nx, int32_t ny, const acm_cnn_net* net, const void* gout, int32_t accumulate,
+                                float* gin, const float* zero_bias, void* stream)
+{
+    if (!net || !gout || !net->workspace || (gin && !zero_bias)) return cfail(ACM_EINVAL, "NULL pointer");
+    for (int l = 0; l < ACM_CNN_LAYERS; ++l)
+        if (!net->acts[l] || !net->wt16[l] || !net->gw[l] || !net->gb[l] || (l < ACM_CNN_LAYERS - 1 && !net->gacts[l]))
+            return cfail(ACM_EINVAL, "NULL layer pointer");
+    const void* g = gout;
+    for (int l = ACM_CNN_LAYERS - 1; l >= 0; --l) {
+        acm_status st = wgrad_impl(nx, ny, NET_CI[l], NET_CO[l], net->acts[l], g, net->workspace, net->gw[l],
+                                   net->gb[l], stream, accumulate ? 1 : 0);
+        if (st != ACM_OK) return st;
+        if (l > 0) {
+            st = acm_cnn_conv(nx, ny, NET_CO[l], NET_CI[l], ACM_CONV_MASK, g, net->wt16[l], nullptr, net->acts[l],
+                              net->gacts[l - 1], stream);
+            g = net->gacts[l - 1];
+        } else if (gin) {
+            st = acm_cnn_conv(nx, ny, NET_CO[0], NET_CI[0], ACM_CONV_RAW, g, net->wt16[0], zero_bias, nullptr, gin,
+                              stream);
+        }
+        if (st != ACM_OK) return st;
+    }
+    return ACM_OK;
+}
+
+acm_status acm_cnn_net_adam(const acm_cnn_net* net, float lr, float b1, float b2, float eps, int64_t t, void* stream)
+{
+    if (!net || t < 1) return cfail(ACM_EINVAL, "bad Adam arguments");
+    NetAdam a;
+    for (int l = 0; l < ACM_CNN_LAYERS; ++l) {
+        a.w[l] = net->w32[l];
+        a.b[l] = net->b32[l];
+        a.gw[l] = net->gw[l];
+        a.gb[l] = net->gb[l];
+        a.mw[l] = net->mw[l];
+        a.vw[l] = net->vw[l];
+        a.mb[l] = net->mb[l];
+        a.vb[l] = net->vb[l];
+        a.w16[l] = static_cast<bf16_t*>(net->w16[l]);
+        a.wt16[l] = static_cast<bf16_t*>(net->wt16[l]);
+        a.cin[l] = NET_CI[l];
+        a.cout[l] = NET_CO[l];
+        if (!a.w[l] || !a.b[l] || !a.gw[l] || !a.gb[l] || !a.mw[l] || !a.vw[l] || !a.mb[l] || !a.vb[l] || !a.w16[l] ||
+            !a.wt16[l])
+            return cfail(ACM_EINVAL, "NULL layer pointer");
+    }
+    const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
+    hipLaunchKernelGGL(net_adam_kernel, dim3(blocks_for(9 * 32 * 32 + 32), ACM_CNN_LAYERS), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), a, lr, b1, b2, eps, c1, c2);
     return chip(hipGetLastError(), "adam launch");
 }
 
