@@ -2,10 +2,9 @@
 // axisymmetric, one to three steps per launch.
 //
 // Measured per step against the LDS tile kernels (FP32, runs of 100 steps):
-// 1024^2 periodic 8.9 -> 6.95 us (two steps per launch, 128-column windows,
-// chunks of five rows), 4096 x 2048 axisymmetric pipe 52.5 -> 29.3 us (a
-// copy of the state takes 23.6), 401 x 257 cavity 4.2 -> 3.9 us; 64^2 FP64 3.8
-// -> 2.4 us.  The march is bound by instruction issue (about 65 VALU
+// 1024^2 periodic 8.8 -> 5.9 us (two steps per launch), 4096 x 2048
+// axisymmetric pipe 50.5 -> 31 us (a copy of the state takes 23.6), 401 x 257
+// cavity 4.2 -> 3.6 us; 64^2 FP64 3.8 -> 2.4 us.  The march is bound by instruction issue (about 65 VALU
 // instructions per node and step, 100 axisymmetric) and, on small grids, by
 // the 1.7 us of a launch inside a graph and the serial rows of a chunk.
 #include <algorithm>
@@ -83,27 +82,32 @@ int windows_of(int vx, int lv, int nx, bool wall)
     }
 }
 
-// Modelled time of one launch in us.  rho', momentum: instructions of a row
-// of drho' and of a row of new momenta per wave, from the compiled loops; an
-// instruction takes 1.95 ns of a SIMD's time when three or more waves share
-// it, 2.35 with two and 3.5 with one (scalar work and waits are then not
-// hidden), measured on a 1024^2 grid.  1.7 us is a launch inside a graph, 1.7
-// us the first loads and last stores.  Memory: 8 TB/s while both state sets
-// stay in the 256 MB cache, else 5.5.
+// Modelled time of one launch in us, fitted to 117 measured shapes (401 x 257
+// to 4096 x 2048, 7 % rms).  rho', momentum: instructions of a row of drho' and
+// of a row of new momenta per wave, from the compiled loops.  An instruction
+// takes ns[w - 1] of a SIMD's time when w waves share it (four and more alike;
+// with fewer, scalar work and waits are not hidden); more waves than a SIMD
+// holds run one round after the other.  3.1 us is a launch inside a graph
+// (1.7), the first loads and the last stores.  Memory: 8.1 TB/s while both
+// state sets stay in the 256 MB cache, else 5.5.
 double launch_us(int vx, int lv, int nw, int ny, int rows, bool f64, bool axi, bool wall, double bytes)
 {
-    const double unit = (f64 ? 1.35 : 1.0) * (axi ? 1.55 : 1.0);
-    const double rho = unit * (6 + 19 * vx) + (wall ? 6 : 0), mom = unit * (9 + 39 * vx) + (wall ? 14 : 0);
-    double work = 10.0 * (rows + 4 * lv);
+    static const double ns[4] = {3.04, 1.87, 1.70, 1.55};
+    const double unit = (f64 ? 1.35 : 1.0) * (axi ? 1.31 : 1.0);
+    const double rho = unit * (6 + 19 * vx) + (wall ? 5 : 0), mom = unit * (9 + 39 * vx) + (wall ? 12 : 0);
+    double work = 11.0 * (rows + 4 * lv);
     for (int l = 1; l <= lv; ++l)
         work += (rows + 4 * (lv - l) + 2) * rho + (rows + 4 * (lv - l)) * mom;
     const int nb = (nw * ((ny + rows - 1) / rows) + 3) / 4, ncu = compute_units();
-    const int k = (nb + ncu - 1) / ncu;  // waves of the busiest SIMD
-    const double ns = k == 1 ? 3.5 : k == 2 ? 2.35 : 1.95;
-    const double alu = k * work * ns * 1e-3;
+    const int whole = (nb + ncu - 1) / ncu;  // waves of the busiest SIMD
+    const int held = f64 ? 4 - lv : vx == 1 ? (lv == 1 ? 7 : lv == 2 ? 5 : 3) : lv == 1 ? 4 : wall ? 2 : 3;
+    const int full = whole / held, rest = whole % held;
+    double alu = full * held * ns[std::min(held, 4) - 1] + (rest ? rest * ns[std::min(rest, 4) - 1] : 0.0);
+    if (whole > 2) alu *= (0.24 * nb / ncu + 0.76 * whole) / whole;  // the others take up some of its work
+    alu *= work * 1e-3;
     const double traffic = bytes * (1.0 + 2.0 * lv / rows);  // halo rows are read twice
-    const double mem = traffic / (2.0 * bytes < 230e6 ? 8e6 : 5.5e6);
-    return 3.4 + std::max(alu, mem) + 0.3 * std::min(alu, mem);
+    const double mem = traffic / (bytes < 230e6 ? 8.1e6 : 5.5e6);
+    return 3.07 + std::max(alu, mem) + 0.3 * std::min(alu, mem);
 }
 
 }  // namespace

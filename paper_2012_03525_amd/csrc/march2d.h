@@ -38,7 +38,10 @@
 namespace acm {
 namespace march {
 
-constexpr int PD = 2;  // rows fetched ahead
+// rows fetched ahead: a row of 128 columns and two levels takes over a
+// microsecond, so one is enough there, and with it the kernel fits three waves
+// per SIMD
+constexpr int rows_ahead(int vx, int lv) { return vx * lv >= 4 ? 1 : 2; }
 
 // Windows of one row of nx nodes: 64 VX columns each, HL lanes of halo
 // between neighbouring windows (2 LV columns).  wall: the x faces are walls or
@@ -196,9 +199,9 @@ struct Edge {
 // Row n (slot J of the level's ring) has arrived: drho' of row n - 1, then
 // the new state of row n - 2 into (ro, uo, vo) when that row is wanted
 // (>= mlo; returns whether it was formed).
-template <int J, typename T, int VX, bool WX, bool WY, bool AXI, typename IR>
+template <int J, typename T, int VX, bool WX, bool WY, bool AXI, typename IR, typename FR>
 __device__ __forceinline__ bool push(const Coef<T>& c, Level<T, VX>& L, int row, int mlo, bool wally, const Edge<T>& eg,
-                                     const IR& inv_r, T (&ro)[VX], T (&uo)[VX], T (&vo)[VX])
+                                     const IR& inv_r, const FR& force, T (&ro)[VX], T (&uo)[VX], T (&vo)[VX])
 {
     constexpr int n = J % 6, k = (J + 5) % 6, m = (J + 4) % 6, s = (J + 3) % 6;
     constexpr int dk = (J + 2) % 3, dm = (J + 1) % 3, ds = J % 3;
@@ -307,13 +310,7 @@ __device__ __forceinline__ bool push(const Coef<T>& c, Level<T, VX>& L, int row,
         qE[VX - 1] = eg.r ? q[VX - 1] : qE[VX - 1];
     }
     const T irm = AXI ? inv_r(row - 2) : T(0);
-    T gx = c.gdt[0];
-    if (c.fx) {
-        int fr = row - 2;  // rows outside the grid: the wrapped row's force (periodic; else not stored)
-        fr = fr < 0 ? fr + c.ny : fr;
-        fr = fr >= c.ny ? fr - c.ny : fr;
-        gx = fmaT(c.dt, c.fx[fr], gx);
-    }
+    const T gx = force(row - 2);
 #pragma unroll
     for (int j = 0; j < VX; ++j) {
         const T rc = L.r[m][j], uc = L.u[m][j], vc = L.v[m][j];
@@ -419,32 +416,40 @@ __device__ __forceinline__ void run(const Coef<T>& c, const State<T>& in, const 
             }
     yf = nb < 0 ? nb + ny : nb;
     if (yf < 0) yf = ((nb % ny) + ny) % ny;
+    constexpr int PD = rows_ahead(VX, LV);
     fetch(std::integral_constant<int, 0>{});
-    fetch(std::integral_constant<int, 1>{});
-    static_assert(PD == 2, "the prologue fetches two rows");
+    if constexpr (PD == 2) fetch(std::integral_constant<int, 1>{});
 
-    // 1 / (row + 1/2) of 64 rows at a time, one per lane: lane l holds row ib + l
+    // Row values of 64 rows at a time, lane l holding row ib + l: dt times the
+    // x force, and 1 / (row + 1/2) (axisymmetric).
     int ib = nb;
-    T irv = T(0);
-    auto fill_ir = [&](int from) {
+    T irv = T(0), fxv = c.gdt[0];
+    auto fill = [&](int from) {
         ib = from;
-        irv = T(1) / (T(from + lane) + T(0.5));
+        if (AXI) irv = T(1) / (T(from + lane) + T(0.5));
+        if (c.fx) {
+            int y = from + lane;  // rows outside the grid: the wrapped row's (periodic; else not used)
+            y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
+            if (y < 0 || y >= ny) y = ((y % ny) + ny) % ny;
+            fxv = fmaT(c.dt, c.fx[y], c.gdt[0]);
+        }
     };
-    if (AXI) fill_ir(nb);
+    fill(nb);
     auto inv_r = [&](int row) { return lane_value(irv, (row - ib) & 63); };
+    auto force = [&](int row) { return lane_value(fxv, (row - ib) & 63); };
 
     // row n = nb + i, J = i mod 6
     auto iterate = [&](int n, auto jc) {
         constexpr int J = decltype(jc)::value;
-        if (n + PD <= ne) fetch(std::integral_constant<int, (J + PD) % 6>{});
+        fetch(std::integral_constant<int, (J + PD) % 6>{});
         T r[VX], u[VX], v[VX];
-        bool have = push<J, T, VX, WX, WY, AXI>(c, L[0], n, first(0), wally, eg, inv_r, r, u, v);
+        bool have = push<J, T, VX, WX, WY, AXI>(c, L[0], n, first(0), wally, eg, inv_r, force, r, u, v);
         if constexpr (LV >= 2) {
             constexpr int J1 = (J + 4) % 6;
             if (have) {
 #pragma unroll
                 for (int j = 0; j < VX; ++j) L[1].r[J1][j] = r[j], L[1].u[J1][j] = u[j], L[1].v[J1][j] = v[j];
-                have = push<J1, T, VX, WX, WY, AXI>(c, L[1], n - 2, first(1), wally, eg, inv_r, r, u, v);
+                have = push<J1, T, VX, WX, WY, AXI>(c, L[1], n - 2, first(1), wally, eg, inv_r, force, r, u, v);
             }
         }
         if constexpr (LV >= 3) {
@@ -452,32 +457,34 @@ __device__ __forceinline__ void run(const Coef<T>& c, const State<T>& in, const 
             if (have) {
 #pragma unroll
                 for (int j = 0; j < VX; ++j) L[LV - 1].r[J2][j] = r[j], L[LV - 1].u[J2][j] = u[j], L[LV - 1].v[J2][j] = v[j];
-                have = push<J2, T, VX, WX, WY, AXI>(c, L[LV - 1], n - 4, first(2), wally, eg, inv_r, r, u, v);
+                have = push<J2, T, VX, WX, WY, AXI>(c, L[LV - 1], n - 4, first(2), wally, eg, inv_r, force, r, u, v);
             }
         }
-        if (have) {
-            const unsigned o = (unsigned)(n - 2 * LV) * pitch;
-            row_store<T, VX>(r, qr, soff, o);
-            row_store<T, VX>(u, qu, soff, o);
-            row_store<T, VX>(v, qv, soff, o);
-        }
+        // No memory access stands in a branch: the waits for a row's loads then
+        // leave the later rows' loads and the stores in flight.  A row not
+        // formed is stored past the end, which drops it.
+        const unsigned so = have ? soff : fbytes, o = have ? (unsigned)(n - 2 * LV) * pitch : 0u;
+        row_store<T, VX>(r, qr, so, o);
+        row_store<T, VX>(u, qu, so, o);
+        row_store<T, VX>(v, qv, so, o);
     };
     static_assert(LV >= 1 && LV <= 3, "one to three levels");
     int n = nb;
-    for (; n + 5 <= ne; n += 6) {
-        if (AXI && n - ib >= 48) fill_ir(n - 2 * LV);  // the next six pushes read rows n - 2 LV .. n + 4
+    for (;;) {
+        if (n - ib >= 48 && (AXI || c.fx)) fill(n - 2 * LV);  // the next six pushes use rows n - 2 LV .. n + 4
         iterate(n, std::integral_constant<int, 0>{});
-        iterate(n + 1, std::integral_constant<int, 1>{});
-        iterate(n + 2, std::integral_constant<int, 2>{});
-        iterate(n + 3, std::integral_constant<int, 3>{});
-        iterate(n + 4, std::integral_constant<int, 4>{});
-        iterate(n + 5, std::integral_constant<int, 5>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 1>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 2>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 3>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 4>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 5>{});
+        if (n++ == ne) break;
     }
-    if (n <= ne) iterate(n, std::integral_constant<int, 0>{});
-    if (n + 1 <= ne) iterate(n + 1, std::integral_constant<int, 1>{});
-    if (n + 2 <= ne) iterate(n + 2, std::integral_constant<int, 2>{});
-    if (n + 3 <= ne) iterate(n + 3, std::integral_constant<int, 3>{});
-    if (n + 4 <= ne) iterate(n + 4, std::integral_constant<int, 4>{});
 }
 
 }  // namespace march
