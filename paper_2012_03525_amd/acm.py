@@ -506,7 +506,8 @@ def ensure_tuned(shapes, precision: int, mode: int = 0, steps: int = 20):
         t = ctypes.c_int32()
         if lib().acm_batch_tuned_tile(nx, ny, precision, mode, ctypes.byref(t)) == OK:
             continue
-        key = f"{arch}/{nx}x{ny}/{'f64' if precision == F64 else 'f32'}/mode{mode}"
+        # mode 0 variants are rows per item ("rows"), mode 1 variants LDS tiles
+        key = f"{arch}/{nx}x{ny}/{'f64' if precision == F64 else 'f32'}/{'rows' if mode == 0 else 'mode1'}"
         if key in disk and 0 <= int(disk[key]) < 6:
             check(lib().acm_batch_set_tuned_tile(nx, ny, precision, mode, int(disk[key])))
             continue

@@ -1,9 +1,12 @@
-// Batched independent 2D cases in one launch per step.
+// Batched independent 2D cases in one launch per step or two.
 //
-// Every active (case, tile) pair is an item of a device table.  Mode 0
-// (default): one workgroup per item slot (the item capacity), slots past the
+// Every active (case, part) pair is an item of a device table.  Mode 0
+// (default): one wave per item slot (the item capacity), slots past the
 // active count exit at once, and the hardware dispatcher keeps as many items
-// in flight as occupancy allows.  Mode 1: a persistent grid (CUs x occupancy
+// in flight as occupancy allows.  An item is a window of columns and a chunk
+// of rows of a case, advanced two steps per launch by the register march
+// (march2d.h); a batch with a case the march does not cover (rho0 other than
+// 1) runs on LDS tiles, one workgroup per (case, tile) and step.  Mode 1: a persistent grid (CUs x occupancy
 // workgroups) pops ranges of `grab` items from an atomic counter, one range
 // ahead, and loads the next item's fields into registers while it computes
 // the current one, so its own load latency overlaps its arithmetic; the tile
@@ -31,6 +34,7 @@
 
 #include "../../include/acm.h"
 #include "acm_internal.h"
+#include "march2d.h"
 #include "tile2d.h"
 
 namespace acm {
@@ -444,7 +448,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     }
 }
 
-// Mode 0: one workgroup per active item; slots past the active count exit.
+// Mode 0, register march: one wave per active item (case, window, first
+// row, row after the last), LV steps, in windows of 64 columns; the rows of a
+// chunk are the case's tile variant (MARCH_ROWS).  The windows are those of
+// two steps for either LV.  Five waves per SIMD (96 VGPRs): 128-column
+// windows take fewer instructions per node but 176 VGPRs, and ran the
+// 512-case sweep at 75 us per step against 54; one workgroup per (case, LDS
+// tile) took 93.
+constexpr int MARCH_LV = 2;
+constexpr int MARCH_ROWS[NTILE2D] = {16, 8, 32, 4, 24, 64};
+using MarchWindows = march::Windows<1, MARCH_LV>;
+template <typename T, int LV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 2))) void batch_march_kernel(
+    const BatchCaseDev<T>* __restrict__ cases_g, const int4* __restrict__ items_g, const int* __restrict__ nitems,
+    int parity)
+{
+    const int n = *nitems, nb = (n + 3) / 4;
+    if ((int)blockIdx.x >= nb) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int item = 4 * xcd_remap(blockIdx.x, nb) + wave;
+    if (item >= n) return;
+    const int4 it = ((ConstItems)items_g)[item];
+    const ConstCases<T> bc = (ConstCases<T>)cases_g + it.x;
+    Coef<T> c;
+    __builtin_memcpy(&c, &bc->c, sizeof c);
+    const State<T> a{bc->s[0].r, bc->s[0].u, bc->s[0].v, nullptr, nullptr};
+    const State<T> b{bc->s[1].r, bc->s[1].u, bc->s[1].v, nullptr, nullptr};
+    const State<T> in = parity ? b : a, out = parity ? a : b;
+    const bool wall = c.bc[0] != BC_PERIODIC;
+    int xs, l0, l1;
+    MarchWindows::window(c.nx, wall, it.y, MarchWindows::count(c.nx, wall), xs, l0, l1);
+    if (c.nonperiodic) march::run<T, 1, LV, true, true, false>(c, in, out, xs, l0, l1, it.z, it.w);
+    else march::run<T, 1, LV, false, false, false>(c, in, out, xs, l0, l1, it.z, it.w);
+}
+
+// Mode 0 on LDS tiles: one workgroup per active item; slots past the active count exit.
 template <typename T>
 __global__ __launch_bounds__(256) void batch_grid_kernel(const BatchCaseDev<T>* __restrict__ cases,
                                                           const int4* __restrict__ items,
@@ -523,7 +561,8 @@ struct acm_batch {
     int chunk = 500;
     int blocks = 0;
     int grab = 2;
-    int mode = 0;   // 0 one workgroup per item, 1 persistent work queue
+    int mode = 0;   // 0 one wave or workgroup per item, 1 persistent work queue
+    bool march = false;   // mode 0 on the register march
     double umax_limit = 0.3;
     hipStream_t stream = nullptr;
     hipStream_t cap = nullptr;
@@ -540,7 +579,7 @@ struct acm_batch {
     std::vector<int> hactive;
     std::vector<double> hhealth;
     size_t max_items = 0;
-    std::vector<int> tile, nx, ny, state;
+    std::vector<int> tile, nx, ny, nw, state;
     std::vector<int64_t> nsteps, done;
     std::vector<double> done_ms, umax;
     hipEvent_t ev_start = nullptr, ev_chunk = nullptr;
@@ -553,15 +592,26 @@ namespace {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Items of one case: (tiles in x) * (tiles in y) of its tile variant; for
-// tile -1 the largest count over the variants, so the scratch size does not
-// depend on the autotuner's choice.
-size_t case_items(int nx, int ny, int tile)
+int march_windows(const acm_config& c) { return MarchWindows::count(c.nx, c.bc[0] != BC_PERIODIC); }
+
+// the register march covers the case (as march2d_plan)
+bool march_ok(const acm_config& c)
+{
+    return c.rho0 == 1.0 && (double)c.nx * c.ny * (c.precision == ACM_F64 ? 8 : 4) < 2147483648.0;
+}
+
+// Items of one case: (tiles in x) * (tiles in y) of its tile variant, or its
+// windows times chunks of rows, whichever is more; for tile -1 the largest
+// count over the variants, so the scratch size does not depend on the
+// autotuner's choice.
+size_t case_items(const acm_config& c, int tile)
 {
     size_t m = 0;
+    const int nw = march_windows(c);
     for (int t = 0; t < NTILE2D; ++t) {
         if (tile >= 0 && t != tile) continue;
-        m = std::max(m, (size_t)((nx + TILE_W[t] - 1) / TILE_W[t]) * ((ny + TILE_H[t] - 1) / TILE_H[t]));
+        m = std::max(m, (size_t)((c.nx + TILE_W[t] - 1) / TILE_W[t]) * ((c.ny + TILE_H[t] - 1) / TILE_H[t]));
+        m = std::max(m, (size_t)nw * ((c.ny + MARCH_ROWS[t] - 1) / MARCH_ROWS[t]));
     }
     return m;
 }
@@ -610,9 +660,16 @@ hipError_t upload_cases(acm_batch* b, const acm_batch_case* cases)
 }
 
 template <typename T>
-hipError_t launch_batch_step(acm_batch* b, int parity, hipStream_t s)
+hipError_t launch_batch_step(acm_batch* b, int parity, int lv, hipStream_t s)
 {
-    if (b->mode == 0)
+    const dim3 march_grid((unsigned)std::max<size_t>(1, (b->max_items + 3) / 4));
+    if (lv == MARCH_LV)
+        hipLaunchKernelGGL((batch_march_kernel<T, MARCH_LV>), march_grid, dim3(256), 0, s,
+                           static_cast<const BatchCaseDev<T>*>(b->dcases), b->ditems, b->dnitems, parity);
+    else if (b->march)
+        hipLaunchKernelGGL((batch_march_kernel<T, 1>), march_grid, dim3(256), 0, s,
+                           static_cast<const BatchCaseDev<T>*>(b->dcases), b->ditems, b->dnitems, parity);
+    else if (b->mode == 0)
         hipLaunchKernelGGL((batch_grid_kernel<T>), dim3((unsigned)std::max<size_t>(1, b->max_items)), dim3(256), 0,
                            s, static_cast<const BatchCaseDev<T>*>(b->dcases), b->ditems, b->dnitems, parity);
     else
@@ -649,9 +706,14 @@ acm_status build_graph(acm_batch* b)
 {
     hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return bfail(ACM_EHIP, std::string("capture: ") + hipGetErrorString(e));
-    for (int i = 0; i < b->chunk; ++i) {
-        e = (b->precision == ACM_F64) ? launch_batch_step<double>(b, i & 1, b->cap)
-                                      : launch_batch_step<float>(b, i & 1, b->cap);
+    // every launch flips the sets, and the chunk ends in set a: the march takes
+    // its two-step launches in pairs, two single steps make up the rest
+    const int pairs = b->march ? b->chunk / 4 * 2 : 0;
+    const int launches = b->chunk - pairs * (MARCH_LV - 1);
+    for (int i = 0; i < launches; ++i) {
+        const int lv = i < pairs ? MARCH_LV : 1;
+        e = (b->precision == ACM_F64) ? launch_batch_step<double>(b, i & 1, lv, b->cap)
+                                      : launch_batch_step<float>(b, i & 1, lv, b->cap);
         if (e != hipSuccess) break;
     }
     hipGraph_t g = nullptr;
@@ -697,7 +759,7 @@ acm_status check_cases(const acm_batch_case* cases, int32_t ncases, const acm_ba
             return bfail(ACM_EINVAL, "batched cases are 2D single-phase planar");
         if (k.cfg.precision != prec) return bfail(ACM_EINVAL, "every case of a batch needs the same precision");
         if (k.tile < -1 || k.tile >= NTILE2D) return bfail(ACM_EINVAL, "tile must be -1..5");
-        items += case_items(k.cfg.nx, k.cfg.ny, k.tile);
+        items += case_items(k.cfg, k.tile);
     }
     if (max_items) *max_items = items;
     return ACM_OK;
@@ -783,18 +845,23 @@ acm_status acm_batch_init(const acm_batch_case* cases, int32_t ncases, const acm
     b->tile.resize(ncases);
     b->nx.resize(ncases);
     b->ny.resize(ncases);
+    b->nw.resize(ncases);
     b->state.assign(ncases, 0);
     b->nsteps.resize(ncases);
     b->done.assign(ncases, 0);
     b->done_ms.assign(ncases, -1.0);
     b->umax.assign(ncases, 0.0);
+    bool march = mode == 0;
     for (int i = 0; i < ncases; ++i) {
         b->tile[i] = tiles[i];
         b->nx[i] = cases[i].cfg.nx;
         b->ny[i] = cases[i].cfg.ny;
         b->nsteps[i] = ((cases[i].nsteps + chunk - 1) / chunk) * chunk;
-        b->max_items += case_items(b->nx[i], b->ny[i], tiles[i]);
+        b->nw[i] = march_windows(cases[i].cfg);
+        march = march && march_ok(cases[i].cfg);
+        b->max_items += case_items(cases[i].cfg, tiles[i]);
     }
+    b->march = march;
     char* base = static_cast<char*>(scratch);
     b->dcases = base + L.cases;
     b->ditems = reinterpret_cast<int4*>(base + L.items);
@@ -850,6 +917,13 @@ acm_status acm_batch_run(acm_batch* b, int32_t max_chunks, int32_t* active_left)
             if (b->state[i] != 0) continue;
             b->hactive[nact++] = i;
             const int t = b->tile[i];
+            if (b->march) {  // chunks of rows, each over the windows of a row
+                for (int y = 0; y < b->ny[i]; y += MARCH_ROWS[t])
+                    for (int w = 0; w < b->nw[i]; ++w)
+                        b->hitems[nit++] = make_int4(i, w, y, std::min(y + MARCH_ROWS[t], b->ny[i]));
+                chunk_lups += (int64_t)b->nx[i] * b->ny[i] * b->chunk;
+                continue;
+            }
             const int tx = (b->nx[i] + TILE_W[t] - 1) / TILE_W[t], ty = (b->ny[i] + TILE_H[t] - 1) / TILE_H[t];
             for (int y = 0; y < ty; ++y)
                 for (int x = 0; x < tx; ++x) b->hitems[nit++] = make_int4(i, x, y, 0);
@@ -934,8 +1008,12 @@ size_t acm_batch_autotune_scratch_bytes(int32_t nx, int32_t ny, int32_t precisio
         return 0;
     }
     const size_t es = precision == ACM_F64 ? 8 : 4;
+    acm_config c{};
+    c.nx = nx;
+    c.ny = ny;
+    c.precision = precision;
     return align256((size_t)nx * ny * es * 6 * (size_t)copies) +
-           batch_layout(copies, case_items(nx, ny, -1) * (size_t)copies, precision).total;
+           batch_layout(copies, case_items(c, -1) * (size_t)copies, precision).total;
 }
 
 acm_status acm_batch_autotune(int32_t nx, int32_t ny, int32_t precision, int32_t mode, int32_t copies, int32_t steps,
