@@ -106,7 +106,9 @@ typedef struct acm_config {
                                nx 64, 128 or 256, ny >= band + 4; else the
                                default); 0: the whole-row kernel with 4-row
                                bands where it applies (chunk chosen for the
-                               CU count), else 13 with 64-plane chunks,
+                               CU count), else for FP32 grids whose two sets
+                               fit 256 MB a register march along z, else 13
+                               with 64-plane chunks,
                                or a smaller shape and chunk (down to 32x8
                                with 4-plane chunks) when that gives fewer
                                than two workgroups per CU (FP64 accepts 3,

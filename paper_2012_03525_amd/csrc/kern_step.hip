@@ -550,6 +550,8 @@ hipError_t launch_step3d(const Coef<T>& c, const State<T>& in, const State<T>& o
         const hipError_t e = launch_step3d_rows<T>(c, in, out, 16, rows_default_chunk(c.ny, c.nz), s);
         if (e != hipErrorInvalidValue) return e;
     }
+    if constexpr (sizeof(T) == 4)  // other grids that stay in the caches
+        if (tile == 0 && march3d_ok(c)) return launch_march3d(c, in, out, s);
     int zc;
     if (tile == 0) {
         const Launch3 d = small_grid_shape(c.nx, c.ny, c.nz, sizeof(T) == 8);
