@@ -20,7 +20,7 @@ __global__ __launch_bounds__(256) void march3d_kernel(Coef<T> c, State<T> in, St
     if (z0 >= c.nz) return;
     int xs, l0, l1;
     W::window(c.nx, WX && c.bc[0] != BC_PERIODIC, w, nw, xs, l0, l1);
-    march::run3<T, VX, RY, WX, WYZ>(c, in, out, xs, l0, l1, by * RY, z0, z1);
+    march::run3<T, VX, RY, WX, WYZ, false>(c, in, out, xs, l0, l1, by * RY, z0, z1);
 }
 
 template <typename T, int VX, int RY, bool WX, bool WYZ>

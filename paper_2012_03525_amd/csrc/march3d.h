@@ -1,7 +1,7 @@
 // 3D single-phase SMAME step as a register march along z: a wave owns a
 // window of 64 VX columns of RY neighbouring x rows and marches them through a
-// chunk of planes; no LDS and no barrier.  FP32, rho0 = 1, any faces, no
-// per-node force.
+// chunk of planes; no LDS and no barrier.  FP32, rho0 = 1, any faces, with
+// (FST) or without the two-phase force.
 //
 // What bounds it and why this layout.  On grids that stay in the caches
 // (below about 200^3) the LDS-staged column march spends its time in
@@ -37,11 +37,12 @@ struct Planes {
     // by plane modulo 3, rows y0 - 1 .. y0 + RY: drho'
     T rn[3][RY + 2][VX];
     T gr[3][RY][VX];        // drho_E - drho_W of the own rows
+    T fs[2][3][RY][VX];     // surface-tension force phi G_iso mu, by plane modulo 2
 };
 
 // RY rows from y0 of planes z0 .. z1 - 1 on the window starting at column xs;
 // lanes l0 .. l1 - 1 store.
-template <typename T, int VX, int RY, bool WX, bool WYZ>
+template <typename T, int VX, int RY, bool WX, bool WYZ, bool FST>
 __device__ __forceinline__ void run3(const Coef<T>& c, const State<T>& in, const State<T>& out, int xs, int l0, int l1,
                                      int y0, int z0, int z1)
 {
@@ -119,6 +120,19 @@ __device__ __forceinline__ void run3(const Coef<T>& c, const State<T>& in, const
             row_load<T, VX>(P.w[sl][i], iw, loff, pz + yoff[i + 1]);
         }
     };
+    // the force of plane p, used when plane p + 2 has arrived
+    auto fetch_force = [&](int p, auto slot) {
+        if constexpr (FST) {
+            constexpr int sl = decltype(slot)::value;
+            const unsigned pz = (unsigned)plane_in(p) * pbytes;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const __amdgpu_buffer_rsrc_t f = field_rsrc(c.fst[a], fbytes);
+#pragma unroll
+                for (int i = 0; i < RY; ++i) row_load<T, VX>(P.fs[sl][a][i], f, loff, pz + yoff[i + 2]);
+            }
+        }
+    };
     // the velocity rule of face f on row i of plane slot sl (u, w rows shifted by one)
     auto rule = [&](int f, auto slot, int i) {
         constexpr int sl = decltype(slot)::value;
@@ -146,6 +160,7 @@ __device__ __forceinline__ void run3(const Coef<T>& c, const State<T>& in, const
                 if (q < 3 && i < RY) P.gr[q][i][j] = T(0);
             }
     fetch(nb, std::integral_constant<int, 0>{});
+    fetch_force(nb - 2, std::integral_constant<int, 0>{});
 
     // plane n = nb + i has arrived (slot J = i mod 6): drho' of plane n - 1, the new state of plane n - 2
     auto iterate = [&](int nn, auto jc) {
@@ -153,6 +168,7 @@ __device__ __forceinline__ void run3(const Coef<T>& c, const State<T>& in, const
         constexpr int n = J % 6, k = (J + 5) % 6, m = (J + 4) % 6, s = (J + 3) % 6;
         constexpr int dk = (J + 2) % 3, dm = (J + 1) % 3, ds = J % 3;
         fetch(nn + 1, std::integral_constant<int, (J + 1) % 6>{});  // (two planes ahead measured the same)
+        fetch_force(nn - 1, std::integral_constant<int, (J + 1) % 2>{});
         if (WYZ) {
             if (wally) {
 #pragma unroll
@@ -301,9 +317,14 @@ __device__ __forceinline__ void run3(const Coef<T>& c, const State<T>& in, const
                     const T sy = (P.rn[dm][i + 2][j] - P.rn[dm][i][j]) - gyr;
                     const T sz = (P.rn[dk][i + 1][j] - P.rn[ds][i + 1][j]) - gzr;
                     const T rho_n = T(1) + rnC;
-                    const T dmx = fmaT(rho_n, gx[i], fmaT(-c.ks, sx, fmaT(c.kv, lpx, -c.cg * fxx)));
-                    const T dmy = fmaT(rho_n, c.gdt[1], fmaT(-c.ks, sy, fmaT(c.kv, lpy, -c.cg * fyy)));
-                    const T dmz = fmaT(rho_n, c.gdt[2], fmaT(-c.ks, sz, fmaT(c.kv, lpz, -c.cg * fzz)));
+                    T dmx = fmaT(rho_n, gx[i], fmaT(-c.ks, sx, fmaT(c.kv, lpx, -c.cg * fxx)));
+                    T dmy = fmaT(rho_n, c.gdt[1], fmaT(-c.ks, sy, fmaT(c.kv, lpy, -c.cg * fyy)));
+                    T dmz = fmaT(rho_n, c.gdt[2], fmaT(-c.ks, sz, fmaT(c.kv, lpz, -c.cg * fzz)));
+                    if constexpr (FST) {  // -dt phi G_iso mu
+                        dmx = fmaT(-c.dt, P.fs[J % 2][0][i][j], dmx);
+                        dmy = fmaT(-c.dt, P.fs[J % 2][1][i][j], dmy);
+                        dmz = fmaT(-c.dt, P.fs[J % 2][2][i][j], dmz);
+                    }
                     const T drn = rnC - rc;
                     const T inv = recipT(rho_n);
                     ro[i][j] = rnC;
