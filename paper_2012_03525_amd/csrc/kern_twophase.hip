@@ -25,9 +25,13 @@
 // LDS: phi^n and mu^n are last read in the phi* phase (which also takes
 // each output node's phi^n and surface-tension force into registers), so
 // mu* and drho' are written over them afterwards; 18.7 KB per 32 x 16 tile
-// lets eight workgroups share a CU.
+// lets eight workgroups share a CU.  The default where walls have no wetting
+// rule is the register march further below.
+#include <algorithm>
+
 #include "acm_internal.h"
 #include "kern_axisym.h"
+#include "march2d.h"
 #include "tile2d.h"
 
 namespace acm {
@@ -350,6 +354,332 @@ __global__ __launch_bounds__(NT) void twophase2d_kernel(Coef<T> c, State<T> in, 
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same step as a register march along y (march2d.h): a wave owns a window
+// of 64 VX columns (four columns of halo on each side) and marches it down a
+// chunk of rows; every stage of the step follows the one before it by a row.
+// When phi of row n arrives,
+//   mu is formed on row n - 1, phi* and the force on row n - 2 (whose flow
+//   arrives then), mu* on row n - 3, phi^{n+1} and the flow on row n - 4.
+// No LDS and no barrier: the tile kernel spends five barriers and 1.6 to 3.1
+// times the nodes of a 32 x 16 tile on its halos (44 x 28 staged for phi); here
+// only a chunk's ends repeat rows, and a row's sums E + W are formed once for
+// the three rows that use them.  Each value is formed by the expressions of the
+// tile kernel in the same order.
+// Bound by vector instructions (about 180 per row and wave of 64).  us per
+// step, tile kernel -> march: 256 x 256 7.7 -> 6.0, 1024 x 1024 18.3 -> 14.5
+// (doubles 26.7 -> 20.7), axisymmetric 2048 x 1024 31.5 -> 23.0 (doubles 49.6
+// -> 35.4), 4096 x 2048 88 -> 51.  Two columns per lane (FP32) halve the halo
+// columns' share: axisymmetric 2048 x 1024 24.7 -> 23.0; small grids lose
+// waves by it (512 x 512 8.3 -> 8.5).
+// ---------------------------------------------------------------------------
+namespace march2p {
+
+// one field of the phase-field pipeline by row modulo 6, and its x sums E + W
+template <typename T, int VX>
+struct Ring {
+    T f[6][VX], s[6][VX];
+};
+
+// rows y0 .. y1 - 1 of the window starting at column xs; lanes l0 .. l1 - 1 store
+template <typename T, int VX, bool WX, bool AXI>
+__device__ __forceinline__ void run(const Coef<T>& c, const State<T>& in, const State<T>& out, int xs, int l0, int l1,
+                                    int y0, int y1)
+{
+    const int nx = c.nx, ny = c.ny, lane = threadIdx.x & 63;
+    const bool wallx = WX && c.bc[0] != BC_PERIODIC, wally = AXI || c.bc[2] != BC_PERIODIC;
+    const unsigned pitch = (unsigned)nx * (unsigned)sizeof(T), fbytes = pitch * (unsigned)ny;
+    int x = xs + VX * lane;
+    if (wallx) {
+        x = min(x, nx - VX);
+    } else {
+        x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
+        if (x < 0 || x >= nx) x = ((x % nx) + nx) % nx;
+    }
+    const unsigned loff = (unsigned)x * (unsigned)sizeof(T);
+    const unsigned soff = (lane >= l0 && lane < l1) ? loff : fbytes;  // past the end: dropped
+    march::Edge<T> eg;
+    eg.l = wallx && xs == 0 && lane == 0;
+    eg.r = wallx && xs + VX * (lane + 1) == nx;
+    eg.any = wallx && (xs == 0 || xs + 64 * VX >= nx);
+    if (WX) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            eg.s[a] = eg.l ? c.fs[0][a] : c.fs[1][a];
+            eg.o[a] = eg.l ? c.fo[0][a] : c.fo[1][a];
+        }
+    }
+    const __amdgpu_buffer_rsrc_t ip = march::field_rsrc(in.phi, fbytes), ir = march::field_rsrc(in.r, fbytes),
+                                 iu = march::field_rsrc(in.u, fbytes), iv = march::field_rsrc(in.v, fbytes),
+                                 qp = march::field_rsrc(out.phi, fbytes), qr = march::field_rsrc(out.r, fbytes),
+                                 qu = march::field_rsrc(out.u, fbytes), qv = march::field_rsrc(out.v, fbytes);
+    // neighbours in x; beyond an x face the node itself (its mirror)
+    typedef T V[VX];
+    auto east_west = [&](const V& f, V& ea, V& we) {
+        march::east_west(f, ea, we);
+        if (WX) {
+            ea[VX - 1] = eg.r ? f[VX - 1] : ea[VX - 1];
+            we[0] = eg.l ? f[0] : we[0];
+        }
+    };
+
+    march::Level<T, VX> L;
+    Ring<T, VX> P, M, PS, MS;  // phi, mu, phi*, mu*
+    T fst[3][2][VX];       // two-phase force by row modulo 3
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int j = 0; j < VX; ++j) {
+            L.r[q][j] = L.u[q][j] = L.v[q][j] = T(0);
+            P.f[q][j] = P.s[q][j] = M.f[q][j] = M.s[q][j] = T(0);
+            PS.f[q][j] = PS.s[q][j] = MS.f[q][j] = MS.s[q][j] = T(0);
+            if (q < 3) {
+                L.mx[q][j] = L.my[q][j] = L.pxy[q][j] = L.pyy[q][j] = T(0);
+                L.rn[q][j] = L.gr[q][j] = fst[q][0][j] = fst[q][1][j] = T(0);
+            }
+        }
+    // a walled bottom face starts at its ghost row; flow rows lag two behind
+    const int nb = wally ? max(y0 - 4, -1) : y0 - 4, ne = y1 + 3;
+    auto wrap = [&](int y) { return wally ? y : ((y % ny) + ny) % ny; };
+    int yp = wrap(nb), yf = wrap(nb - 2);  // next rows to fetch
+    auto row_of = [&](int& y) {
+        const int r = wally ? min(max(y, 0), ny - 1) : y;
+        y = !wally && y + 1 == ny ? 0 : y + 1;
+        return (unsigned)r * pitch;
+    };
+    auto fetch = [&](auto slot) {
+        constexpr int sl = decltype(slot)::value;
+        march::row_load<T, VX>(P.f[sl], ip, loff, row_of(yp));
+        const unsigned o = row_of(yf);
+        march::row_load<T, VX>(L.r[sl], ir, loff, o);
+        march::row_load<T, VX>(L.u[sl], iu, loff, o);
+        march::row_load<T, VX>(L.v[sl], iv, loff, o);
+    };
+    constexpr int PD = VX == 1 ? 2 : 1;
+    fetch(std::integral_constant<int, 0>{});
+    if constexpr (PD == 2) fetch(std::integral_constant<int, 1>{});
+
+    // dt times the x force and 1 / (row + 1/2) of 64 rows at a time, lane l holding row ib + l
+    int ib = nb;
+    T irv = T(0), fxv = c.gdt[0];
+    auto fill = [&](int from) {
+        ib = from;
+        if (AXI) irv = T(1) / (T(from + lane) + T(0.5));
+        if (c.fx) fxv = fmaT(c.dt, c.fx[min(max(from + lane, 0), ny - 1)], c.gdt[0]);
+    };
+    fill(nb);
+    auto inv_r = [&](int row) { return march::lane_value(irv, (row - ib) & 63); };
+    auto force = [&](int row) { return march::lane_value(fxv, (row - ib) & 63); };
+
+    // sums of the D2Q9 stencils around row b (N above, S below), in the order of liso_num, gisox_num, gisoy_num
+    typedef Ring<T, VX> Rows;
+    auto gy = [&](const Rows& A, int nn, int ss, int j) {
+        return fmaT(T(4), A.f[nn][j] - A.f[ss][j], A.s[nn][j] - A.s[ss][j]);
+    };
+    auto gx = [&](const Rows& A, int nn, int b, int ss, V& g) {
+        V t, fe, fw, te, tw;
+#pragma unroll
+        for (int j = 0; j < VX; ++j) t[j] = A.f[nn][j] + A.f[ss][j];
+        east_west(A.f[b], fe, fw);
+        east_west(t, te, tw);
+#pragma unroll
+        for (int j = 0; j < VX; ++j) g[j] = fmaT(T(4), fe[j] - fw[j], te[j] - tw[j]);
+    };
+    auto lap0 = [&](const Rows& A, int nn, int b, int ss, int j) {
+        return fmaT(T(4), A.s[b][j] + (A.f[nn][j] + A.f[ss][j]), A.s[nn][j] + A.s[ss][j]) - T(20) * A.f[b][j];
+    };
+    auto lap = [&](const Rows& A, int nn, int b, int ss, T hirc, int j) {
+        const T l = lap0(A, nn, b, ss, j);
+        if constexpr (AXI) return fmaT(hirc, gy(A, nn, ss, j), l);
+        else return l;
+    };
+    auto chem = [&](const Rows& A, int nn, int b, int ss, T irc, V& m) {
+#pragma unroll
+        for (int j = 0; j < VX; ++j) {
+            const T p = A.f[b][j];
+            m[j] = fmaT(c.a4 * p, fmaT(p, p, T(-1)), -c.kap6 * lap0(A, nn, b, ss, j));
+            if constexpr (AXI) m[j] = fmaT(T(-0.5) * c.kap6 * irc, gy(A, nn, ss, j), m[j]);
+        }
+    };
+    auto sums = [&](Rows& A, int b) {
+        V ea, we;
+        east_west(A.f[b], ea, we);
+#pragma unroll
+        for (int j = 0; j < VX; ++j) A.s[b][j] = ea[j] + we[j];
+    };
+    // ghost row of an intermediate: row 0 is the mirror of row -1, row ny - 1 of row ny
+    auto ghost = [&](Rows& A, int row, int b, int ss) {
+#pragma unroll
+        for (int j = 0; j < VX; ++j) {
+            if (wally && row == 0) A.f[ss][j] = A.f[b][j], A.s[ss][j] = A.s[b][j];
+            if (wally && row == ny) A.f[b][j] = A.f[ss][j], A.s[b][j] = A.s[ss][j];
+        }
+    };
+
+    // phi of row n and the flow of row n - 2 have arrived (slot J): mu of row
+    // n - 1, phi* and the force of row n - 2, mu* of row n - 3, the new state of row n - 4
+    auto iterate = [&](int n, auto jc) {
+        constexpr int J = decltype(jc)::value;
+        constexpr int a = J, b = (J + 5) % 6, d = (J + 4) % 6, e = (J + 3) % 6, f = (J + 2) % 6, h = (J + 1) % 6;
+        V pn, r, u, v, g, pc;  // pc: phi of row n - 4, whose slot the fetch takes
+#pragma unroll
+        for (int j = 0; j < VX; ++j) pc[j] = P.f[f][j];
+        fetch(std::integral_constant<int, (J + PD) % 6>{});
+        sums(P, a);
+        if (n - 1 >= y0 - 3) {
+            chem(P, a, b, d, AXI ? inv_r(n - 1) : T(0), M.f[b]);
+            sums(M, b);
+            ghost(M, n - 1, b, d);
+        }
+        bool have = false;
+        if (n - 2 >= y0 - 2) {
+            const T hirc = AXI ? T(0.5) * inv_r(n - 2) : T(0);
+            gx(P, b, d, e, g);
+#pragma unroll
+            for (int j = 0; j < VX; ++j) {
+                const T adv = fmaT(L.u[J][j], g[j], L.v[J][j] * gy(P, b, e, j)) * c.gi;
+                const T rhs = fmaT(c.mob * c.li, lap(M, b, d, e, hirc, j), -adv);
+                PS.f[d][j] = fmaT(c.dt, rhs, P.f[d][j]);
+            }
+            sums(PS, d);
+            ghost(PS, n - 2, d, e);
+            gx(M, b, d, e, g);
+#pragma unroll
+            for (int j = 0; j < VX; ++j) {
+                fst[J % 3][0][j] = -c.dt * P.f[d][j] * (g[j] * c.gi);
+                fst[J % 3][1][j] = -c.dt * P.f[d][j] * (gy(M, b, e, j) * c.gi);
+            }
+            if (n - 3 >= y0 - 1) {
+                chem(PS, d, e, f, AXI ? inv_r(n - 3) : T(0), MS.f[e]);
+                sums(MS, e);
+                ghost(MS, n - 3, e, f);
+            }
+            if (n - 4 >= y0) {
+                const T hirc2 = AXI ? T(0.5) * inv_r(n - 4) : T(0);
+                constexpr int o = (J + 4) % 6;
+                gx(PS, e, f, h, g);
+#pragma unroll
+                for (int j = 0; j < VX; ++j) {
+                    const T adv = fmaT(L.u[o][j], g[j], L.v[o][j] * gy(PS, e, h, j)) * c.gi;
+                    const T rhs = fmaT(c.mob * c.li, lap(MS, e, f, h, hirc2, j), -adv);
+                    pn[j] = T(0.5) * fmaT(c.dt, rhs, pc[j] + PS.f[f][j]);
+                }
+            }
+            have = march::push<J, T, VX, WX, true, AXI>(c, L, n - 2, y0, wally, eg, inv_r, force, r, u, v,
+                                                        fst[(J + 1) % 3]);
+        }
+        const unsigned so = have ? soff : fbytes, o = have ? (unsigned)(n - 4) * pitch : 0u;
+        march::row_store<T, VX>(r, qr, so, o);
+        march::row_store<T, VX>(u, qu, so, o);
+        march::row_store<T, VX>(v, qv, so, o);
+        march::row_store<T, VX>(pn, qp, so, o);
+    };
+    int n = nb;
+    for (;;) {
+        if (n - ib >= 48 && (AXI || c.fx)) fill(n - 5);  // the next six iterations use rows n - 4 .. n + 4
+        iterate(n, std::integral_constant<int, 0>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 1>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 2>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 3>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 4>{});
+        if (n++ == ne) break;
+        iterate(n, std::integral_constant<int, 5>{});
+        if (n++ == ne) break;
+    }
+}
+
+template <typename T, int VX, bool WX, bool AXI>
+__global__ __launch_bounds__(256) void twophase_march_kernel(Coef<T> c, State<T> in, State<T> out, int nw, int rows)
+{
+    const int item = 4 * xcd_remap(blockIdx.x, gridDim.x) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int chunk = item / nw, w = item - chunk * nw;
+    const int y0 = chunk * rows, y1 = min(y0 + rows, c.ny);
+    if (y0 >= c.ny) return;
+    int xs, l0, l1;
+    march::Windows<VX, 2>::window(c.nx, WX && c.bc[0] != BC_PERIODIC, w, nw, xs, l0, l1);
+    run<T, VX, WX, AXI>(c, in, out, xs, l0, l1, y0, y1);
+}
+
+int compute_units()
+{
+    static const int ncu = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+            return 256;
+        return n;
+    }();
+    return ncu;
+}
+
+// Modelled time of one launch in us, fitted to 380 measured shapes (96 x 96 to
+// 2048 x 1024, 2.6 % rms).  us[w - 1]: time of one row of one wave, per wave,
+// when w waves share a SIMD; more waves than a SIMD holds run one round after
+// the other.  3.1 rows stand for the eight halo rows, which are formed in part.
+double launch_us(int vx, int nw, int ny, int rows, bool f64, bool axi, double bytes)
+{
+    static const double f32_1[4] = {0.593, 0.398, 0.369, 0.329}, f32_2[2] = {0.838, 0.618}, f64_1[2] = {0.775, 0.575};
+    const double* us = f64 ? f64_1 : vx == 2 ? f32_2 : f32_1;
+    const int ncu = compute_units();
+    const int nb = (nw * ((ny + rows - 1) / rows) + 3) / 4, held = us == f32_1 ? 4 : 2;
+    const int whole = (nb + ncu - 1) / ncu, full = whole / held, rest = whole % held;
+    double alu = full * held * us[held - 1] + (rest ? rest * us[rest - 1] : 0.0);
+    if (whole > 2) alu *= (0.19 * nb / ncu + 0.81 * whole) / whole;
+    alu *= (rows + 3.1) * (axi ? 1.05 : 1.0);
+    const double mem = bytes * (1.0 + 2.0 / rows) / (bytes < 230e6 ? 8.1e6 : 5.5e6);
+    return 2.9 + std::max(alu, mem) + 0.3 * std::min(alu, mem);
+}
+
+// Launch shape: columns per lane and rows per chunk; vx = 0: not marched.
+struct Plan {
+    int vx, rows;
+};
+
+// The shape with the least modelled time.  Not marched: wetting walls (their
+// ghosts take a rule of their own), rho0 != 1, and in planar doubles the sizes
+// where the tile kernel's 32 x 16 tiles come to at most two per compute unit
+// and the march needs more than 10.5 us: 512 x 512 10.5 us with tiles, 11.0
+// marched, but 512 x 400 10.9 and 10.2, 560 x 512 12.7 and 11.9.
+
+template <typename T>
+Plan plan(const Coef<T>& c, bool axi)
+{
+    Plan best{0, 0};
+    const bool f64 = sizeof(T) == 8, wall = c.bc[0] != BC_PERIODIC;
+    const double nodes = (double)c.nx * c.ny;
+    if (c.wet || c.rho0 != T(1) || nodes * sizeof(T) >= 2147483648.0) return best;
+    double least = 0.0;
+    for (int vx = 1; vx <= (f64 ? 1 : 2); ++vx) {
+        if (vx == 2 && !march::Windows<2, 2>::fits(c.nx, wall)) continue;
+        const int nw = vx == 2 ? march::Windows<2, 2>::count(c.nx, wall) : march::Windows<1, 2>::count(c.nx, wall);
+        for (int r = 1; r <= 64 && r <= c.ny; ++r) {
+            const double t = launch_us(vx, nw, c.ny, r, f64, axi, 8.0 * nodes * sizeof(T));
+            if (best.vx == 0 || t < least) best = Plan{vx, r}, least = t;
+        }
+    }
+    if (f64 && !axi && least > 10.5 && ((c.nx + 31) / 32) * ((c.ny + 15) / 16) <= 2 * compute_units()) best.vx = 0;
+    return best;
+}
+
+template <typename T, int VX, bool AXI>
+hipError_t launch_vx(const Coef<T>& c, const State<T>& in, const State<T>& out, int rows, hipStream_t s)
+{
+    const bool wall = c.bc[0] != BC_PERIODIC;
+    const int nw = march::Windows<VX, 2>::count(c.nx, wall);
+    const int nb = (nw * ((c.ny + rows - 1) / rows) + 3) / 4;
+    if (wall)
+        hipLaunchKernelGGL((twophase_march_kernel<T, VX, true, AXI>), dim3(nb), dim3(256), 0, s, c, in, out, nw, rows);
+    else
+        hipLaunchKernelGGL((twophase_march_kernel<T, VX, false, AXI>), dim3(nb), dim3(256), 0, s, c, in, out, nw, rows);
+    return hipGetLastError();
+}
+
+}  // namespace march2p
+
 template <typename T, int TX, int TY, int NT, bool AXI>
 static hipError_t launch2p_variant(const Coef<T>& c, const State<T>& in, const State<T>& out, hipStream_t s)
 {
@@ -361,6 +691,12 @@ static hipError_t launch2p_variant(const Coef<T>& c, const State<T>& in, const S
 template <typename T, bool AXI>
 static hipError_t launch2p(const Coef<T>& c, const State<T>& in, const State<T>& out, int tile, hipStream_t s)
 {
+    if (tile == 0) {
+        const march2p::Plan p = march2p::plan(c, AXI);
+        if constexpr (sizeof(T) == 4)
+            if (p.vx == 2) return march2p::launch_vx<T, 2, AXI>(c, in, out, p.rows, s);
+        if (p.vx == 1) return march2p::launch_vx<T, 1, AXI>(c, in, out, p.rows, s);
+    }
     switch (tile) {
         case 1: return launch2p_variant<T, 32, 8, 256, AXI>(c, in, out, s);
         case 2: return launch2p_variant<T, 64, 8, 256, AXI>(c, in, out, s);

@@ -196,12 +196,16 @@ struct Edge {
     T s[2], o[2];  // the face's velocity rule u_g = s u + o (u, v), per lane
 };
 
+struct NoForce {};
+
 // Row n (slot J of the level's ring) has arrived: drho' of row n - 1, then
 // the new state of row n - 2 into (ro, uo, vo) when that row is wanted
-// (>= mlo; returns whether it was formed).
-template <int J, typename T, int VX, bool WX, bool WY, bool AXI, typename IR, typename FR>
+// (>= mlo; returns whether it was formed).  fst: the two-phase force on row
+// n - 2, -dt phi G_iso mu (fst[axis][node]), or NoForce.
+template <int J, typename T, int VX, bool WX, bool WY, bool AXI, typename IR, typename FR, typename FS = NoForce>
 __device__ __forceinline__ bool push(const Coef<T>& c, Level<T, VX>& L, int row, int mlo, bool wally, const Edge<T>& eg,
-                                     const IR& inv_r, const FR& force, T (&ro)[VX], T (&uo)[VX], T (&vo)[VX])
+                                     const IR& inv_r, const FR& force, T (&ro)[VX], T (&uo)[VX], T (&vo)[VX],
+                                     const FS& fst = FS())
 {
     constexpr int n = J % 6, k = (J + 5) % 6, m = (J + 4) % 6, s = (J + 3) % 6;
     constexpr int dk = (J + 2) % 3, dm = (J + 1) % 3, ds = J % 3;
@@ -336,8 +340,13 @@ __device__ __forceinline__ bool push(const Coef<T>& c, Level<T, VX>& L, int row,
         const T sx = (qE[j] - qW[j]) - L.gr[dm][j];
         const T sy = (L.rn[dk][j] - L.rn[ds][j]) - (rN - rS);
         const T rho_n = rho0 + rnC;
-        const T dmx = fmaT(rho_n, gx, fmaT(-c.ks, sx, fmaT(c.kv, lx, -c.cg * fxx)));
-        const T dmy = fmaT(rho_n, c.gdt[1], fmaT(-c.ks, sy, fmaT(c.kv, ly, -c.cg * fyy)));
+        T px = -c.cg * fxx, py = -c.cg * fyy;
+        if constexpr (!std::is_same<FS, NoForce>::value) {
+            px = fmaT(-c.cg, fxx, fst[0][j]);
+            py = fmaT(-c.cg, fyy, fst[1][j]);
+        }
+        const T dmx = fmaT(rho_n, gx, fmaT(-c.ks, sx, fmaT(c.kv, lx, px)));
+        const T dmy = fmaT(rho_n, c.gdt[1], fmaT(-c.ks, sy, fmaT(c.kv, ly, py)));
         const T drn = rnC - rc;
         const T inv = recipT(rho_n);
         ro[j] = rnC;
