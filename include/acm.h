@@ -440,7 +440,7 @@ acm_status acm_cnn_to_bf16(size_t n, const float* src, void* dst, void* stream);
  * gradients and Adam moments, the bf16 weights and their transposed copies
  * (acm_cnn_transpose), the bf16 input activations and, for layers 1..4, the
  * bf16 gradient with respect to the pre-activation that produced acts[l]
- * (gacts[l - 1]); raw: the fp32 output (16 channels); workspace: the largest
+ * (gacts[l - 1]); raw: the fp32 output (16 channels); workspace: twice the largest
  * acm_cnn_wgrad_workspace of the layers.  All device memory of the caller. */
 typedef struct acm_cnn_net {
     float *w32[ACM_CNN_LAYERS], *b32[ACM_CNN_LAYERS];

@@ -85,7 +85,7 @@ class Network:
         self.gout = torch.zeros((ny, nx, 16), dtype=b16, device=self.dev)
         self.gacts = [torch.zeros((ny, nx, co), dtype=b16, device=self.dev) for _, co in self.shapes]
         ws = max(acm.lib().acm_cnn_wgrad_workspace(nx, ny, ci, co) for ci, co in self.shapes)
-        self.wg_ws = torch.zeros(ws // 4 + 1, dtype=f32, device=self.dev)
+        self.wg_ws = torch.zeros(2 * (ws // 4) + 1, dtype=f32, device=self.dev)
         self.loss_ws = torch.zeros(acm.lib().acm_cnn_loss_workspace(nx, ny) // 8 + 1, dtype=torch.float64,
                                    device=self.dev)
         self.loss_buf = torch.zeros(1, dtype=torch.float64, device=self.dev)

@@ -93,20 +93,22 @@ struct ConvK {
     }
 };
 
+constexpr int conv_lds_bytes(int cin, int tr = 4) { return (tr + 2) * 34 * cin * 2; }
+
 template <int CIN, int COUT, int MODE, int TR = 4>
-__global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const bf16_t* __restrict__ x,
-                                                      const bf16_t* __restrict__ w, const float* __restrict__ bias,
-                                                      const bf16_t* __restrict__ mask, void* __restrict__ y,
-                                                      Correct cr)
+__device__ __forceinline__ void conv3x3_tile(char* lds, int tile, int H, int W, const bf16_t* __restrict__ x,
+                                             const bf16_t* __restrict__ w, const float* __restrict__ bias,
+                                             const bf16_t* __restrict__ mask, void* __restrict__ y, const Correct& cr)
 {
     using K = ConvK<CIN>;
     using op = typename K::op;
     constexpr int TC = 32, IR = TR + 2, IC = TC + 2;
     constexpr int KS = K::KS, KB = K::KB, KW = K::KW, NH = COUT / 16, CH4 = CIN / 4;
     constexpr int NG = TR / 2;  // 16-pixel groups per wave
-    __shared__ __align__(16) bf16_t sx[IR * IC * CIN];
+    static_assert(IR * IC * CIN * 2 == conv_lds_bytes(CIN, TR), "LDS of the tile");
+    bf16_t* const sx = reinterpret_cast<bf16_t*>(lds);
     const int tiles_x = W / TC;
-    const int x0 = (blockIdx.x % tiles_x) * TC, y0 = (blockIdx.x / tiles_x) * TR;
+    const int x0 = (tile % tiles_x) * TC, y0 = (tile / tiles_x) * TR;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l16 = lane & 15, lg = lane >> 4;
     op bw[9][KS][NH];
@@ -198,6 +200,16 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const bf16_t
     }
 }
 
+template <int CIN, int COUT, int MODE, int TR = 4>
+__global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const bf16_t* __restrict__ x,
+                                                      const bf16_t* __restrict__ w, const float* __restrict__ bias,
+                                                      const bf16_t* __restrict__ mask, void* __restrict__ y,
+                                                      Correct cr)
+{
+    __shared__ __align__(16) char lds[conv_lds_bytes(CIN, TR)];
+    conv3x3_tile<CIN, COUT, MODE, TR>(lds, blockIdx.x, H, W, x, w, bias, mask, y, cr);
+}
+
 // ---------------------------------------------------------------------------
 // weight gradient: dW[t][o][i] = sum_p g[p][o] x[p + off(t)][i], db[o] = sum_p g[p][o]
 // Workgroup tile 4 rows x 64 columns; x (with halo) and g are staged in LDS
@@ -216,18 +228,19 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const bf16_t
 // wave, a 32 -> 32 layer took 22.4 us on 256^2 (now 11.6 us).
 // ---------------------------------------------------------------------------
 constexpr int WG_TR = 4, WG_TC = 64;
+constexpr int wgrad_lds_bytes(int cin, int cout) { return ((WG_TR + 2) * cin + WG_TR * cout) * (WG_TC + 8) * 2; }
 
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void conv_wgrad_kernel(int H, int W, const bf16_t* __restrict__ x,
-                                                         const bf16_t* __restrict__ g, float* __restrict__ partial)
+__device__ __forceinline__ void wgrad_tile(char* lds, int tile, int H, int W, const bf16_t* __restrict__ x,
+                                           const bf16_t* __restrict__ g, float* __restrict__ partial)
 {
     // channel rows of x: columns x0-1 .. x0+64 and padding; of g: columns x0 .. x0+63
     // and padding (row strides of 144 bytes)
     constexpr int XR = WG_TR + 2, XC = WG_TC + 8, GC = WG_TC + 8;
-    __shared__ __align__(16) bf16_t sxT[XR][CIN][XC];
-    __shared__ __align__(16) bf16_t sgT[WG_TR][COUT][GC];
+    bf16_t(*const sxT)[CIN][XC] = reinterpret_cast<bf16_t(*)[CIN][XC]>(lds);
+    bf16_t(*const sgT)[COUT][GC] = reinterpret_cast<bf16_t(*)[COUT][GC]>(lds + XR * CIN * XC * 2);
     const int tiles_x = W / WG_TC;
-    const int x0 = (blockIdx.x % tiles_x) * WG_TC, y0 = (blockIdx.x / tiles_x) * WG_TR;
+    const int x0 = (tile % tiles_x) * WG_TC, y0 = (tile / tiles_x) * WG_TR;
     // items (row, eight channels, column pair) of x, then of g
     constexpr int XP = (WG_TC + 2) / 2, XI = XR * (CIN / 8) * XP;
     constexpr int GP = WG_TC / 2, GI = WG_TR * (COUT / 8) * GP;
@@ -320,7 +333,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(int H, int W, const bf1
             }
         }
     }
-    float* part = partial + (size_t)blockIdx.x * (9 * COUT * CIN + COUT);
+    float* part = partial + (size_t)tile * (9 * COUT * CIN + COUT);
 #pragma unroll
     for (int s = 0; s < PER; ++s) {
         const int tr = wave + 4 * s;
@@ -344,39 +357,93 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(int H, int W, const bf1
     }
 }
 
-// fixed-order sum of the per-workgroup partials: out[e] = sum_b partial[b][e]
-// (acc: out[e] += that sum).  A workgroup takes 64 consecutive elements;
-// wave s of its RP_SEG waves sums the blocks b = s, s + RP_SEG, ... in
-// increasing b (64 consecutive floats of a partial row per load), and the
-// RP_SEG segment sums are added in increasing s: a fixed order for any
-// launch, with RP_SEG independent load streams per element.
-constexpr int RP_SEG = 16;
-__global__ __launch_bounds__(64 * RP_SEG) void reduce_partials_kernel(const float* __restrict__ partial, int nblk,
-                                                                      int n, float* __restrict__ dw,
-                                                                      float* __restrict__ db, int nw, int acc)
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256) void conv_wgrad_kernel(int H, int W, const bf16_t* __restrict__ x,
+                                                         const bf16_t* __restrict__ g, float* __restrict__ partial)
 {
-    __shared__ float seg[RP_SEG][64];
-    const int lane = threadIdx.x & 63, sgi = threadIdx.x >> 6;
-    const int e = blockIdx.x * 64 + lane;
-    float s = 0.f;
-    if (e < n) {
-        int b = sgi;
-        // four loads in flight per lane; the sum stays in increasing b
-        for (; b + 3 * RP_SEG < nblk; b += 4 * RP_SEG) {
-            const float v0 = partial[(size_t)b * n + e], v1 = partial[(size_t)(b + RP_SEG) * n + e];
-            const float v2 = partial[(size_t)(b + 2 * RP_SEG) * n + e], v3 = partial[(size_t)(b + 3 * RP_SEG) * n + e];
-            s = (((s + v0) + v1) + v2) + v3;
+    __shared__ __align__(16) char lds[wgrad_lds_bytes(CIN, COUT)];
+    wgrad_tile<CIN, COUT>(lds, blockIdx.x, H, W, x, g, partial);
+}
+
+// fixed-order sum of the per-workgroup partials: out[e] = sum_b partial[b][e]
+// (acc: out[e] += that sum).  A workgroup takes 64 consecutive elements.  The
+// blocks are summed in RP_SEG segments, segment s taking b = s, s + RP_SEG, ...
+// in increasing b, and the segment sums are added in increasing s: a fixed
+// order for any launch.  Wave w of the four sums segments w, w + 4, ...
+// together.
+constexpr int RP_SEG = 16, RP_LDS = RP_SEG * 64 * 4;
+struct Partials {
+    const float* partial;  // NULL: nothing to reduce
+    int nblk, n, nw, acc;
+    float *dw, *db;
+};
+__device__ __forceinline__ void reduce_tile(char* lds, int tile, const Partials& p)
+{
+    float(*const seg)[64] = reinterpret_cast<float(*)[64]>(lds);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int e = tile * 64 + lane;
+    constexpr int PER = RP_SEG / 4;
+    float s[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) s[k] = 0.f;
+    if (e < p.n) {
+        int b = wave;
+        for (; b + 3 * RP_SEG + 4 * (PER - 1) < p.nblk; b += 4 * RP_SEG) {  // sixteen loads in flight
+            float v[4][PER];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int k = 0; k < PER; ++k) v[i][k] = p.partial[(size_t)(b + i * RP_SEG + 4 * k) * p.n + e];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int k = 0; k < PER; ++k) s[k] += v[i][k];
         }
-        for (; b < nblk; b += RP_SEG) s += partial[(size_t)b * n + e];
+        for (; b < p.nblk; b += RP_SEG)
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if (b + 4 * k < p.nblk) s[k] += p.partial[(size_t)(b + 4 * k) * p.n + e];
     }
-    seg[sgi][lane] = s;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) seg[wave + 4 * k][lane] = s[k];
     __syncthreads();
-    if (sgi == 0 && e < n) {
+    if (wave == 0 && e < p.n) {
         float t = seg[0][lane];
         for (int k = 1; k < RP_SEG; ++k) t += seg[k][lane];
-        float* dst = e < nw ? &dw[e] : &db[e - nw];
-        *dst = acc ? *dst + t : t;
+        float* dst = e < p.nw ? &p.dw[e] : &p.db[e - p.nw];
+        *dst = p.acc ? *dst + t : t;
     }
+}
+__global__ __launch_bounds__(256) void reduce_partials_kernel(Partials p)
+{
+    __shared__ __align__(16) char lds[RP_LDS];
+    reduce_tile(lds, blockIdx.x, p);
+}
+
+// ---------------------------------------------------------------------------
+// One layer of the backward pass of the whole network in one launch: its
+// weight-gradient tiles, the data gradient through it (a convolution of the
+// same g), and the reduction of the partials that the layer above left.  None
+// needs another of them; each alone leaves the chip waiting for its first
+// loads (256^2: 256 and 512 workgroups of one wave per SIMD, 145 of the
+// reduction) and costs a launch.  Bound by those waits still: a 32 -> 32 layer
+// on 256^2 took 10.9 + 6.1 + 3.8 us in three launches, 12.7 in one; a training
+// step of two unrolled solver steps 302 us before, 245 now.  Workgroups of the
+// weight gradient, the longest, come first.
+// ---------------------------------------------------------------------------
+template <int CIN, int COUT, int MODE>
+__global__ __launch_bounds__(256) void backward_layer_kernel(int H, int W, const bf16_t* __restrict__ x,
+                                                             const bf16_t* __restrict__ g, float* __restrict__ partial,
+                                                             const bf16_t* __restrict__ wt,
+                                                             const float* __restrict__ bias, void* __restrict__ y,
+                                                             int nconv, Partials above)
+{
+    constexpr int A = wgrad_lds_bytes(CIN, COUT), B = conv_lds_bytes(COUT), C = A > B ? A : B;
+    __shared__ __align__(16) char lds[C > RP_LDS ? C : RP_LDS];
+    const int nwg = (W / WG_TC) * (H / WG_TR), b = blockIdx.x;
+    if (b < nwg) wgrad_tile<CIN, COUT>(lds, b, H, W, x, g, partial);
+    else if (b < nwg + nconv) conv3x3_tile<COUT, CIN, MODE>(lds, b - nwg, H, W, g, wt, bias, x, y, Correct{});
+    else reduce_tile(lds, b - nwg - nconv, above);
 }
 
 // wt[t][i][o] = w[8 - t][o][i]: weights of the transposed convolution
@@ -1306,8 +1373,8 @@ static acm_status wgrad_impl(int32_t nx, int32_t ny, int32_t cin, int32_t cout, 
     acm_status st = chip(hipGetLastError(), "wgrad launch");
     if (st != ACM_OK) return st;
     const int n = 9 * cout * cin + cout;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((n + 63) / 64), dim3(64 * RP_SEG), 0, s, workspace, nblk, n, dw,
-                       db, 9 * cout * cin, acc);
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((n + 63) / 64), dim3(256), 0, s,
+                       Partials{workspace, nblk, n, 9 * cout * cin, acc, dw, db});
     return chip(hipGetLastError(), "reduce launch");
 }
 
@@ -1507,22 +1574,34 @@ acm_status acm_cnn_net_backward(int32_t nx, int32_t ny, const acm_cnn_net* net, 
     for (int l = 0; l < ACM_CNN_LAYERS; ++l)
         if (!net->acts[l] || !net->wt16[l] || !net->gw[l] || !net->gb[l] || (l < ACM_CNN_LAYERS - 1 && !net->gacts[l]))
             return cfail(ACM_EINVAL, "NULL layer pointer");
-    const void* g = gout;
+    if (!grid_ok(nx, ny)) return cfail(ACM_EINVAL, "network grids need nx % 64 == 0 and ny % 8 == 0");
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int nwg = (nx / WG_TC) * (ny / WG_TR), conv_tiles = (nx / 32) * (ny / 4);
+    const size_t half = (size_t)nwg * (9 * 32 * 32 + 32);  // the layers write the halves of the workspace in turn
+    const bf16_t* g = static_cast<const bf16_t*>(gout);
+    Partials above{};
     for (int l = ACM_CNN_LAYERS - 1; l >= 0; --l) {
-        acm_status st = wgrad_impl(nx, ny, NET_CI[l], NET_CO[l], net->acts[l], g, net->workspace, net->gw[l],
-                                   net->gb[l], stream, accumulate ? 1 : 0);
+        const bf16_t *x = static_cast<const bf16_t*>(net->acts[l]), *wt = static_cast<const bf16_t*>(net->wt16[l]);
+        float* part = net->workspace + (l & 1) * half;
+        const int nconv = l > 0 || gin ? conv_tiles : 0, nred = above.partial ? (above.n + 63) / 64 : 0;
+        const dim3 grid(nwg + nconv + nred), block(256);
+        if (l == 0)
+            hipLaunchKernelGGL((backward_layer_kernel<16, 32, CONV_RAW>), grid, block, 0, s, ny, nx, x, g, part, wt,
+                               zero_bias, static_cast<void*>(gin), nconv, above);
+        else if (l == ACM_CNN_LAYERS - 1)
+            hipLaunchKernelGGL((backward_layer_kernel<32, 16, CONV_MASK>), grid, block, 0, s, ny, nx, x, g, part, wt,
+                               nullptr, net->gacts[l - 1], nconv, above);
+        else
+            hipLaunchKernelGGL((backward_layer_kernel<32, 32, CONV_MASK>), grid, block, 0, s, ny, nx, x, g, part, wt,
+                               nullptr, net->gacts[l - 1], nconv, above);
+        const acm_status st = chip(hipGetLastError(), "backward launch");
         if (st != ACM_OK) return st;
-        if (l > 0) {
-            st = acm_cnn_conv(nx, ny, NET_CO[l], NET_CI[l], ACM_CONV_MASK, g, net->wt16[l], nullptr, net->acts[l],
-                              net->gacts[l - 1], stream);
-            g = net->gacts[l - 1];
-        } else if (gin) {
-            st = acm_cnn_conv(nx, ny, NET_CO[0], NET_CI[0], ACM_CONV_RAW, g, net->wt16[0], zero_bias, nullptr, gin,
-                              stream);
-        }
-        if (st != ACM_OK) return st;
+        const int nw = 9 * NET_CO[l] * NET_CI[l];
+        above = Partials{part, nwg, nw + NET_CO[l], nw, accumulate ? 1 : 0, net->gw[l], net->gb[l]};
+        if (l > 0) g = static_cast<const bf16_t*>(net->gacts[l - 1]);
     }
-    return ACM_OK;
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((above.n + 63) / 64), dim3(256), 0, s, above);
+    return chip(hipGetLastError(), "reduce launch");
 }
 
 acm_status acm_cnn_net_adam(const acm_cnn_net* net, float lr, float b1, float b2, float eps, int64_t t, void* stream)
