@@ -545,7 +545,12 @@ static int rows_default_chunk(int ny, int nz)
 template <typename T>
 hipError_t launch_step3d(const Coef<T>& c, const State<T>& in, const State<T>& out, int tile, hipStream_t s)
 {
-    if (tile == 0 && step3d_rows_ok(c) && c.ny >= 8) {
+    // Rows of 64 nodes leave the row kernel one node per lane: on larger boxes
+    // the register march is ahead (64 x 128 x 128: 15.7 us with rows, 13.7
+    // marched; 64 x 200 x 160 23.9 and 21.1; but 64^3 6.9 and 7.8).
+    bool narrow = false;
+    if constexpr (sizeof(T) == 4) narrow = c.nx == 64 && (double)c.ny * c.nz >= 8192.0 && march3d_ok(c);
+    if (tile == 0 && step3d_rows_ok(c) && c.ny >= 8 && !narrow) {
         // whole x rows per wave: the fastest shape where it applies
         const hipError_t e = launch_step3d_rows<T>(c, in, out, 16, rows_default_chunk(c.ny, c.nz), s);
         if (e != hipErrorInvalidValue) return e;

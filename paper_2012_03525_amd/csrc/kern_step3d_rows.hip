@@ -84,18 +84,18 @@ __device__ __forceinline__ void row_load(float (&d)[VX], __amdgpu_buffer_rsrc_t 
     }
 }
 
-// streaming store (the new state is not read again in this step)
-template <int VX>
+// STREAM: streaming store (the new state is not read again in this step)
+template <int VX, bool STREAM>
 __device__ __forceinline__ void row_store(const float (&d)[VX], __amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff)
 {
     if constexpr (VX == 4) {
         const f32x4 q = {d[0], d[1], d[2], d[3]};
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q), r, off, soff, 2);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q), r, off, soff, STREAM ? 2 : 0);
     } else if constexpr (VX == 2) {
         const f32x2 q = {d[0], d[1]};
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, q), r, off, soff, 2);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, q), r, off, soff, STREAM ? 2 : 0);
     } else {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, d[0]), r, off, soff, 2);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, d[0]), r, off, soff, STREAM ? 2 : 0);
     }
 }
 
@@ -155,7 +155,7 @@ struct Rows3 {
     static constexpr size_t lds_bytes = (size_t)(2 * 2 * NRR + 3 * NUR) * NX * sizeof(float);
 };
 
-template <int VX, int NW, bool WIDE, int PD>
+template <int VX, int NW, bool WIDE, int PD, bool STREAM>
 __global__ __launch_bounds__(NW * 64) void step3d_rows_kernel(Coef<float> c, State<float> in, State<float> out,
                                                                int zc, int nby)
 {
@@ -325,10 +325,10 @@ __global__ __launch_bounds__(NW * 64) void step3d_rows_kernel(Coef<float> c, Sta
                                          vo[j], wo[j]);
             }
             const PlaneAccess<WIDE, float> po(out, k, plane, pbytes, fbytes);
-            row_store<VX>(ro, po.r, stoff, po.soff);
-            row_store<VX>(uo, po.u, stoff, po.soff);
-            row_store<VX>(vo, po.v, stoff, po.soff);
-            row_store<VX>(wo, po.w, stoff, po.soff);
+            row_store<VX, STREAM>(ro, po.r, stoff, po.soff);
+            row_store<VX, STREAM>(uo, po.u, stoff, po.soff);
+            row_store<VX, STREAM>(vo, po.v, stoff, po.soff);
+            row_store<VX, STREAM>(wo, po.w, stoff, po.soff);
         }
 #pragma unroll
         for (int j = 0; j < VX; ++j) {
@@ -379,13 +379,21 @@ static hipError_t launch_rows(const Coef<float>& c, const State<float>& in, cons
     constexpr int PD = ROWS_PREFETCH;
     if (c.ny < TY + 4) return hipErrorInvalidValue;
     const int nby = (c.ny + TY - 1) / TY, nbz = (c.nz + zc - 1) / zc;
-    const bool wide = (size_t)c.nx * c.ny * c.nz * sizeof(float) >= (size_t(1) << 31);
-    if (!wide)
-        hipLaunchKernelGGL((step3d_rows_kernel<VX, NW, false, PD>), dim3(nby * nbz), dim3(NW * 64), 0, s, c, in, out,
-                           zc, nby);
+    const double bytes = 32.0 * c.nx * c.ny * c.nz;  // both state sets
+    const dim3 grid(nby * nbz), block(NW * 64);
+    // Streaming stores where the next step finds the state neither in the L2
+    // caches (32 MB) nor in the 256 MB cache behind them, or in the L2 anyway;
+    // plain ones between.  us per step, streaming and plain: 64^3 (8 MB) 6.9
+    // and 7.2, 256 x 64 x 64 (34 MB) 13.6 and 14.1, 128^3 (67 MB) 26.0 and 23.2,
+    // 128 x 200 x 160 (131 MB) 43.1 and 37.1, 256 x 200 x 160 (262 MB) 67.7 and
+    // 61.2, 256 x 256 x 160 (336 MB) 87.6 and 91.1, 256^3 (537 MB) 121 and 126.
+    const bool stream = bytes < 48e6 || bytes > 310e6;
+    if (4.0 * c.nx * c.ny * c.nz >= 2147483648.0)
+        hipLaunchKernelGGL((step3d_rows_kernel<VX, NW, true, PD, true>), grid, block, 0, s, c, in, out, zc, nby);
+    else if (stream)
+        hipLaunchKernelGGL((step3d_rows_kernel<VX, NW, false, PD, true>), grid, block, 0, s, c, in, out, zc, nby);
     else
-        hipLaunchKernelGGL((step3d_rows_kernel<VX, NW, true, PD>), dim3(nby * nbz), dim3(NW * 64), 0, s, c, in, out,
-                           zc, nby);
+        hipLaunchKernelGGL((step3d_rows_kernel<VX, NW, false, PD, false>), grid, block, 0, s, c, in, out, zc, nby);
     return hipGetLastError();
 }
 
