@@ -96,7 +96,7 @@ def workload(name, tile, chunk=100):
         st = inputs.tgv2d(n, 0.01, noise=1e-6)
         meta = {"workload": "2D periodic Taylor-Green vortex 64^2, FP64", "grid": [n, n], "u0": 0.01, "nu": 0.01}
         bytes_per_lup = 48
-        kernel = "step2d_kernel"
+        kernel = "march2d_kernel"
     elif name == "pipe_axisym_4096x2048":
         # axisymmetric pipe (x axial, periodic; y radial: axis, wall at r = R = 2048): start-up of the
         # axially forced flow from a perturbed profile; g sets the Poiseuille centre speed to 0.05
@@ -108,7 +108,7 @@ def workload(name, tile, chunk=100):
         meta = {"workload": "axisymmetric pipe flow 4096 (axial) x 2048 (radial), FP32 drho storage",
                 "grid": [nxa, R], "nu": nu, "g": g}
         bytes_per_lup = 24  # read drho,u,v + write drho,u,v (FP32)
-        kernel = "axisym2d_kernel"
+        kernel = "march2d_kernel (axisymmetric)"
     elif name == "drop_axisym_2048x1024":
         # axisymmetric two-phase: a drop (sphere) of radius 256 on the axis of an axially periodic
         # 2048 x 1024 domain with a symmetry rim, relaxing under surface tension
@@ -119,7 +119,7 @@ def workload(name, tile, chunk=100):
         meta = {"workload": "axisymmetric two-phase drop on the axis 2048 (axial) x 1024 (radial), FP32",
                 "grid": [nxa, nr], "R": R, "W": W, "sigma": 0.01, "mobility": 0.1, "nu": 0.1}
         bytes_per_lup = 32  # read drho,u,v,phi + write them (FP32)
-        kernel = "twophase2d_kernel (axisymmetric)"
+        kernel = "twophase_march_kernel (axisymmetric)"
     elif name == "drop_spreading_96":
         # drop spreading on a wall (Sec. 3.6): N_L = 32, c = 10, Re = 100 (Oh = 0.1), Cn = 0.1,
         # Pe = 8000, theta = 60 degrees; [0,3]^3 with symmetry planes at the sides, walls at z = 0, 3
@@ -138,7 +138,7 @@ def workload(name, tile, chunk=100):
                 "N_L": NL, "c": c, "Re": Re, "Cn": Cn, "Pe": Pe, "theta_deg": theta, "nu": nu, "sigma": sigma,
                 "mobility": M}
         bytes_per_lup = 40  # read drho,u,v,w,phi + write them (FP32), the fused minimum
-        kernel = "twophase3d step (3 launches)"
+        kernel = "twophase3d step (2 launches)"
     else:
         n = 1024
         wu = [[0.0] * 3 for _ in range(6)]
@@ -151,7 +151,7 @@ def workload(name, tile, chunk=100):
         meta = {"workload": "2D two-phase drop in simple shear 1024^2, FP32", "grid": [n, n], "R": 128, "W": 4,
                 "mobility": 0.02, "u_wall": 0.02, "nu": round(1.0 / 6.0, 6), "sigma": 0.01, "steps_of_case": 20000}
         bytes_per_lup = 32
-        kernel = "twophase2d_kernel"
+        kernel = "twophase_march_kernel"
     return cfg, st, meta, bytes_per_lup, kernel
 
 
@@ -219,7 +219,7 @@ def run_batch(a, copy):
         "wall_ms": r["wall_ms"],
         "case_completion_ms": {"p50": r["p50_ms"], "p99": r["p99_ms"], "finished": r["finished"],
                                "diverged": r["diverged"]},
-        "roofline": {"bound": "hbm", "kernel": ["batch_grid_kernel", "batch_step_kernel"][a.batch_mode],
+        "roofline": {"bound": "hbm", "kernel": ["batch_march_kernel", "batch_step_kernel"][a.batch_mode],
                      "achieved": r["gbs"],
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(r["gbs"] / HBM_PEAK_GBS, 4), "traffic": None,
                      "bytes_per_lup": 24, "copy_kernel_gbs": copy["gbs"]},

@@ -92,8 +92,9 @@ typedef struct acm_config {
                                rho0 other than 1 and fields of 2 GiB and
                                more).  2D axisymmetric: 1 32x8, 2 64x8, 4
                                64x4 (0: register march, else 32x16).  2D
-                               two-phase: 1 32x8,
-                               2 64x8, 3 16x16 (0: 32x16).  3D: low byte
+                               two-phase: 1 32x8, 2 64x8, 3 16x16 (0:
+                               register march where no wall has a wetting
+                               rule and rho0 = 1, else 32x16).  3D: low byte
                                1 32x8, 2 64x8, 3 32x4, 4 64x4, 5 64x16,
                                7 32x16, 9 128x4, 12 128x8, 13 64x8 with two
                                rows per thread on fully periodic grids
@@ -106,15 +107,19 @@ typedef struct acm_config {
                                nx 64, 128 or 256, ny >= band + 4; else the
                                default); 0: the whole-row kernel with 4-row
                                bands where it applies (chunk chosen for the
-                               CU count), else for FP32 grids whose two sets
+                               CU count; not rows of 64 nodes on 8192 of
+                               them and more), else for FP32 grids whose two sets
                                fit 256 MB a register march along z, else 13
                                with 64-plane chunks,
                                or a smaller shape and chunk (down to 32x8
                                with 4-plane chunks) when that gives fewer
                                than two workgroups per CU (FP64 accepts 3,
                                4, else 32x8); bits 8+ = z chunk / 16 (0:
-                               64 planes).  Results do not depend on the
-                               tile. */
+                               64 planes).  3D two-phase: the flow step's
+                               shape; 0 (FP32, no wetting rule on the x
+                               faces, rho0 = 1, up to 9 million nodes):
+                               register marches along z, two launches a
+                               step.  Results do not depend on the tile. */
     double wet_cos[6];      /* two-phase: cos(contact angle) of each wall face
                                for the wetting condition of Sec. 2,
                                d_n phi = -(2/W) cos(theta) (1 - phi_w^2),
@@ -240,9 +245,12 @@ const char* acm_last_error(void);
 /* Batched independent 2D cases (serving-style sweeps)                       */
 /* ------------------------------------------------------------------------ */
 /* Hundreds of independent single-phase 2D cases of uneven size advance
- * together: each step is ONE launch over the active (case, tile) items,
- * either persistent workgroups claiming them from atomic work queues or one
- * workgroup per item (acm_batch_opts.mode), applying the same per-node
+ * together: one launch covers the items of every active case, by default
+ * two steps per launch with one wave per item (a window of columns and a
+ * chunk of rows, marched in registers; one workgroup per LDS tile and one
+ * step per launch where a case has rho0 other than 1), or persistent
+ * workgroups claiming (case, tile) items from atomic work queues, one step
+ * per launch (acm_batch_opts.mode), applying the same per-node
  * arithmetic as acm_step (results are bitwise equal to running each case
  * alone).  Steps are captured in HIP graphs of `chunk` steps; after every
  * chunk a health check retires cases that finished or diverged. */
@@ -253,7 +261,9 @@ typedef struct acm_batch_case {
     acm_fields a, b;       /* caller-owned state sets; initial state in a    */
     const void* force_x;   /* NULL or ny values added to g[0] on row j       */
     int64_t nsteps;        /* steps to run (rounded up to whole chunks)      */
-    int32_t tile;          /* 2D tile variant 0..5, or -1: the tile recorded
+    int32_t tile;          /* launch variant 0..5 (mode 0: rows per item 16,
+                              8, 32, 4, 24, 64; mode 1 and mode 0 with rho0
+                              other than 1: 2D tile), or -1: the one recorded
                               for this (nx, ny, precision, launch mode) by
                               acm_batch_autotune / acm_batch_set_tuned_tile  */
 } acm_batch_case;
@@ -265,8 +275,8 @@ typedef struct acm_batch_opts {
     int32_t grab;          /* mode 1: items per claim on the work queue once
                               a workgroup's fixed share is done; 0 = 2       */
     double umax_limit;     /* max |u| above this marks divergence; 0 = 0.3   */
-    int32_t mode;          /* 0: one workgroup per (case, tile) item,
-                              launched over the item capacity; 1: persistent
+    int32_t mode;          /* 0: one wave (rho0 other than 1: workgroup) per
+                              item, launched over the item capacity; 1: persistent
                               workgroups (blocks) in eight XCD groups, each
                               group over a contiguous range of the items:
                               fixed shares over half the range, then claims
@@ -316,7 +326,7 @@ acm_status acm_batch_timing(const acm_batch* b, double* total_ms, int64_t* latti
 void acm_batch_destroy(acm_batch* b);
 
 /* Tile autotuner: time `copies` periodic nx x ny cases for `steps` steps
- * (even) with every 2D tile variant (0..5) through the batched kernel in the
+ * (even) with every launch variant (0..5) through the batched kernel in the
  * given launch mode; ms_per_tile[6] receives ms per step, *best the fastest
  * variant, which is also recorded for (nx, ny, precision, mode) for the
  * life of the process (the choice changes only speed, never results).

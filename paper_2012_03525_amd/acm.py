@@ -364,7 +364,7 @@ BATCH_RUNNING, BATCH_FINISHED, BATCH_DIVERGED = 0, 1, 2
 
 class Batch:
     """Independent 2D single-phase cases advanced together by the batched
-    kernel (mode 0: one workgroup per item; 1: persistent work queue).  All
+    kernel (mode 0: one wave per item; 1: persistent work queue).  All
     states live in one arena tensor (6 fields per case: set a then set b),
     sliced into per-case views.  `forces`, if given, holds per case None or
     the ny values of a row force added to g[0] (kept on the device for the
@@ -453,7 +453,7 @@ class Batch:
 
 def autotune(nx: int, ny: Optional[int] = None, precision: str = "f32", copies: int = 0, steps: int = 100,
              mode: int = 0):
-    """Time every 2D tile variant on copies of a periodic nx x ny case through
+    """Time every launch variant (mode 0: rows per item; 1: tiles) on copies of a periodic nx x ny case through
     the batched kernel; the library records the fastest for (nx, ny,
     precision, mode).  Returns (best_tile, ms_per_step_per_tile)."""
     import torch

@@ -252,7 +252,7 @@ __global__ __launch_bounds__(NTH) void stage2_kernel(Coef<T> c, State<T> in, con
 //   G_z = 2 (f_U - f_D) + (s_U - s_D) + (t_U - t_D),
 // the sums of lap_num, gx_num, gy_num and gz_num in the same order.
 // Bound by instruction issue (vector and scalar together fill the slots; the
-// unrolled loops of 43 to 74 KB miss the instruction cache on 2 % of fetches).
+// unrolled loops of 36 to 66 KB miss the instruction cache on 2 % of fetches).
 // Whole two-phase step, LDS kernels -> march, in us, drop between walls in z:
 // 32^3 31.0 -> 16.5, 64^3 33.7 -> 21.9, 96^3 51.5 -> 40.8, 128^3 94 -> 75.
 // RY = 4 needs 228 to 256 registers: 55 on 96^3.  Two planes loaded ahead
