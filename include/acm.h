@@ -252,8 +252,10 @@ const char* acm_last_error(void);
  * workgroups claiming (case, tile) items from atomic work queues, one step
  * per launch (acm_batch_opts.mode), applying the same per-node
  * arithmetic as acm_step (results are bitwise equal to running each case
- * alone).  Steps are captured in HIP graphs of `chunk` steps; after every
- * chunk a health check retires cases that finished or diverged. */
+ * alone).  Steps are captured in HIP graphs of `chunk` steps; every chunk
+ * ends with a single step, the newest state in set a and the state one step
+ * back in set b.  After every chunk a health check retires cases that
+ * finished or diverged. */
 typedef struct acm_batch acm_batch;
 
 typedef struct acm_batch_case {

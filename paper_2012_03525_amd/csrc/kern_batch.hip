@@ -706,9 +706,10 @@ acm_status build_graph(acm_batch* b)
 {
     hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return bfail(ACM_EHIP, std::string("capture: ") + hipGetErrorString(e));
-    // every launch flips the sets, and the chunk ends in set a: the march takes
-    // its two-step launches in pairs, two single steps make up the rest
-    const int pairs = b->march ? b->chunk / 4 * 2 : 0;
+    // every launch flips the sets, and the chunk ends in set a with a single
+    // step, so that set b holds the state one step back: the march takes its
+    // two-step launches in pairs, two or four single steps make up the rest
+    const int pairs = b->march ? (b->chunk - 2) / 4 * 2 : 0;
     const int launches = b->chunk - pairs * (MARCH_LV - 1);
     for (int i = 0; i < launches; ++i) {
         const int lv = i < pairs ? MARCH_LV : 1;
