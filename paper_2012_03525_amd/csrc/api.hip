@@ -285,11 +285,12 @@ hipError_t launch_multi(const acm_handle* h, int from, hipStream_t s)
                                  h->multi, s);
 }
 
-// How many multi-step launches nsteps steps begin with; single steps follow.  The last step is a single one, so the other set then holds the
-// state one step back, and every launch flips the sets: with two steps per
-// launch their count is kept even, so that the newest state lies in the set
-// it would lie in after single steps (three steps per launch flip like three
-// single steps do).
+// How many multi-step launches nsteps steps begin with; single steps follow.
+// The last step is a single one, so the other set then holds the state one
+// step back, and every launch flips the sets: with two steps per launch their
+// count is kept even, so that the newest state lies in the set it would lie
+// in after single steps (three steps per launch flip like three single steps
+// do).
 int64_t multi_launches(const acm_handle* h, int64_t nsteps)
 {
     if (h->multi.lv < 2 || nsteps < 2) return 0;
@@ -297,14 +298,20 @@ int64_t multi_launches(const acm_handle* h, int64_t nsteps)
     return h->multi.lv % 2 ? n : n - n % 2;
 }
 
-// nsteps steps from set `from` on stream s, launch by launch
-hipError_t launch_steps(const acm_handle* h, int from, int64_t nsteps, hipStream_t s)
+// nsteps steps from set `from` on stream s, launch by launch; done counts the
+// launches that succeeded and their steps
+struct Enqueued {
+    int64_t launches = 0, steps = 0;
+};
+hipError_t launch_steps(const acm_handle* h, int from, int64_t nsteps, hipStream_t s, Enqueued& done)
 {
     const int64_t m = multi_launches(h, nsteps), n = nsteps - m * (h->multi.lv - 1);
-    for (int64_t i = 0; i < n; ++i) {
-        const int f = (int)((from + i) & 1);
-        const hipError_t e = i < m ? launch_multi(h, f, s) : launch_one(h, f, s);
+    for (; done.launches < n; ++done.launches) {
+        const int f = (int)((from + done.launches) & 1);
+        const bool multi = done.launches < m;
+        const hipError_t e = multi ? launch_multi(h, f, s) : launch_one(h, f, s);
         if (e != hipSuccess) return e;
+        done.steps += multi ? h->multi.lv : 1;
     }
     return hipSuccess;
 }
@@ -319,16 +326,18 @@ hipError_t launch_pair(const acm_handle* h, int from, hipStream_t s)
                                      h->cfg.tile, s);
 }
 
-// a graph of chunk steps from set `parity`: chunk one-step launches, or
-// chunk / 2 two-step launches
+// a graph of chunk steps from set `parity`: the launches of launch_steps, or
+// (pair) chunk / 2 two-step launches
 acm_status build_graph(acm_handle* h, int parity, bool pair)
 {
     hipError_t e = hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     if (pair)
         for (int i = 0; i < h->chunk / 2 && e == hipSuccess; ++i) e = launch_pair(h, (parity + i) & 1, h->cap);
-    else
-        e = launch_steps(h, parity, h->chunk, h->cap);
+    else {
+        Enqueued done;
+        e = launch_steps(h, parity, h->chunk, h->cap, done);
+    }
     if (e != hipSuccess) {
         hipGraph_t g = nullptr;
         (void)hipStreamEndCapture(h->cap, &g);
@@ -491,10 +500,11 @@ acm_status acm_run(acm_handle* h, int64_t nsteps)
         nsteps -= h->chunk;
     }
     if (nsteps > 0) {
-        hipError_t e = launch_steps(h, h->which, nsteps, h->stream);
+        Enqueued done;
+        const hipError_t e = launch_steps(h, h->which, nsteps, h->stream, done);
+        h->which ^= (int)(done.launches & 1);
+        h->step += done.steps;
         if (e != hipSuccess) return hip_fail(e, "step launch");
-        h->which ^= (int)(nsteps & 1);
-        h->step += nsteps;
     }
     return ACM_OK;
 }
