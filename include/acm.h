@@ -247,8 +247,9 @@ const char* acm_last_error(void);
 /* Hundreds of independent single-phase 2D cases of uneven size advance
  * together: one launch covers the items of every active case, by default
  * two steps per launch with one wave per item (a window of columns and a
- * chunk of rows, marched in registers; one workgroup per LDS tile and one
- * step per launch where a case has rho0 other than 1), or persistent
+ * chunk of rows, marched in registers; the rows follow from the load; one
+ * workgroup per LDS tile and one step per launch where acm_batch_on_tiles
+ * says so), or persistent
  * workgroups claiming (case, tile) items from atomic work queues, one step
  * per launch (acm_batch_opts.mode), applying the same per-node
  * arithmetic as acm_step (results are bitwise equal to running each case
@@ -263,10 +264,9 @@ typedef struct acm_batch_case {
     acm_fields a, b;       /* caller-owned state sets; initial state in a    */
     const void* force_x;   /* NULL or ny values added to g[0] on row j       */
     int64_t nsteps;        /* steps to run (rounded up to whole chunks)      */
-    int32_t tile;          /* launch variant 0..5 (mode 0: rows per item 16,
-                              8, 32, 4, 24, 64; mode 1 and mode 0 with rho0
-                              other than 1: 2D tile), or -1: the one recorded
-                              for this (nx, ny, precision, launch mode) by
+    int32_t tile;          /* 2D tile variant 0..5 (used where the batch runs
+                              on LDS tiles), or -1: the tile recorded for
+                              this (nx, ny, precision, launch mode) by
                               acm_batch_autotune / acm_batch_set_tuned_tile  */
 } acm_batch_case;
 
@@ -277,8 +277,8 @@ typedef struct acm_batch_opts {
     int32_t grab;          /* mode 1: items per claim on the work queue once
                               a workgroup's fixed share is done; 0 = 2       */
     double umax_limit;     /* max |u| above this marks divergence; 0 = 0.3   */
-    int32_t mode;          /* 0: one wave (rho0 other than 1: workgroup) per
-                              item, launched over the item capacity; 1: persistent
+    int32_t mode;          /* 0: one wave (on LDS tiles: workgroup) per item,
+                              launched over the item capacity; 1: persistent
                               workgroups (blocks) in eight XCD groups, each
                               group over a contiguous range of the items:
                               fixed shares over half the range, then claims
@@ -294,9 +294,16 @@ typedef struct acm_batch_case_status {
     double umax;           /* max |u| at the last health check               */
 } acm_batch_case_status;
 
+/* *on_tiles = 1 where acm_batch_init would run these cases on LDS tiles (mode
+ * 1, or mode 0 with a case of rho0 other than 1 or of 2 GiB per field and
+ * more), 0 where it would run them on the register march, which uses no tile
+ * variant.  Pure host call. */
+acm_status acm_batch_on_tiles(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts,
+                              int32_t* on_tiles);
+
 /* Bytes of device scratch acm_batch_init needs for these cases and options:
- * the case records, the item table (for a case with tile -1 sized for the
- * variant with the most tiles), the item count, the queue counters (eight
+ * the case records, the item table (on LDS tiles, for a case with tile -1,
+ * sized for the variant with the most tiles), the item count, the queue counters (eight
  * group counters 128 bytes apart and a done counter: 1028 bytes), the
  * active list and the health pairs, each part 256-byte aligned.  Returns 0
  * and sets acm_last_error when a case or option is invalid.  Pure host call. */
@@ -328,8 +335,8 @@ acm_status acm_batch_timing(const acm_batch* b, double* total_ms, int64_t* latti
 void acm_batch_destroy(acm_batch* b);
 
 /* Tile autotuner: time `copies` periodic nx x ny cases for `steps` steps
- * (even) with every launch variant (0..5) through the batched kernel in the
- * given launch mode; ms_per_tile[6] receives ms per step, *best the fastest
+ * (even) with every 2D tile variant (0..5) through the batched kernel on LDS
+ * tiles in the given launch mode; ms_per_tile[6] receives ms per step, *best the fastest
  * variant, which is also recorded for (nx, ny, precision, mode) for the
  * life of the process (the choice changes only speed, never results).
  * scratch: device memory of acm_batch_autotune_scratch_bytes bytes,

@@ -96,6 +96,8 @@ SIGNATURES = {
     "acm_last_error": (ctypes.c_char_p, []),
     "acm_version": (ctypes.c_char_p, []),
     "acm_stream_copy": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]),
+    "acm_batch_on_tiles": (ctypes.c_int, [ctypes.POINTER(BatchCase), ctypes.c_int32, ctypes.POINTER(BatchOpts),
+                                          ctypes.POINTER(ctypes.c_int32)]),
     "acm_batch_scratch_bytes": (ctypes.c_size_t, [ctypes.POINTER(BatchCase), ctypes.c_int32,
                                                   ctypes.POINTER(BatchOpts)]),
     "acm_batch_init": (ctypes.c_int, [ctypes.POINTER(BatchCase), ctypes.c_int32, ctypes.POINTER(BatchOpts),
@@ -405,7 +407,13 @@ class Batch:
         self.stream = torch.cuda.current_stream()
         untuned = {(c.nx, c.ny) for i, c in enumerate(cfgs) if tiles is None or int(tiles[i]) < 0}
         if untuned:
-            ensure_tuned(sorted(untuned), prec, mode)
+            on_tiles = ctypes.c_int32()
+            check(lib().acm_batch_on_tiles(arr, n, ctypes.byref(opts), ctypes.byref(on_tiles)))
+            if on_tiles.value:
+                ensure_tuned(sorted(untuned), prec, mode)
+            else:  # the register march takes no tile variant
+                for bc in arr:
+                    bc.tile = max(bc.tile, 0)
         nbytes = lib().acm_batch_scratch_bytes(arr, n, ctypes.byref(opts))
         if nbytes == 0:
             raise AcmError(EINVAL, lib().acm_last_error().decode())
@@ -453,8 +461,8 @@ class Batch:
 
 def autotune(nx: int, ny: Optional[int] = None, precision: str = "f32", copies: int = 0, steps: int = 100,
              mode: int = 0):
-    """Time every launch variant (mode 0: rows per item; 1: tiles) on copies of a periodic nx x ny case through
-    the batched kernel; the library records the fastest for (nx, ny,
+    """Time every 2D tile variant on copies of a periodic nx x ny case through
+    the batched kernel on LDS tiles; the library records the fastest for (nx, ny,
     precision, mode).  Returns (best_tile, ms_per_step_per_tile)."""
     import torch
     ny = nx if ny is None else ny
@@ -506,8 +514,7 @@ def ensure_tuned(shapes, precision: int, mode: int = 0, steps: int = 20):
         t = ctypes.c_int32()
         if lib().acm_batch_tuned_tile(nx, ny, precision, mode, ctypes.byref(t)) == OK:
             continue
-        # mode 0 variants are rows per item ("rows"), mode 1 variants LDS tiles
-        key = f"{arch}/{nx}x{ny}/{'f64' if precision == F64 else 'f32'}/{'rows' if mode == 0 else 'mode1'}"
+        key = f"{arch}/{nx}x{ny}/{'f64' if precision == F64 else 'f32'}/mode{mode}"
         if key in disk and 0 <= int(disk[key]) < 6:
             check(lib().acm_batch_set_tuned_tile(nx, ny, precision, mode, int(disk[key])))
             continue

@@ -449,14 +449,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 }
 
 // Mode 0, register march: one wave per active item (case, window, first
-// row, row after the last), LV steps, in windows of 64 columns; the rows of a
-// chunk are the case's tile variant (MARCH_ROWS).  The windows are those of
-// two steps for either LV.  Five waves per SIMD (96 VGPRs): 128-column
-// windows take fewer instructions per node but 176 VGPRs, and ran the
-// 512-case sweep at 75 us per step against 54; one workgroup per (case, LDS
-// tile) took 93.
+// row, row after the last), LV steps, in windows of 64 columns; the rows of an
+// item follow from the load (march_rows).  The windows are those of two steps
+// for either LV.  Five waves per SIMD (96 VGPRs): 128-column windows take
+// fewer instructions per node but 176 VGPRs, and ran the 512-case sweep at 75
+// us per step against 54; one workgroup per (case, LDS tile) took 93.
 constexpr int MARCH_LV = 2;
-constexpr int MARCH_ROWS[NTILE2D] = {16, 8, 32, 4, 24, 64};
 using MarchWindows = march::Windows<1, MARCH_LV>;
 template <typename T, int LV>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 2))) void batch_march_kernel(
@@ -563,6 +561,7 @@ struct acm_batch {
     int grab = 2;
     int mode = 0;   // 0 one wave or workgroup per item, 1 persistent work queue
     bool march = false;   // mode 0 on the register march
+    int rows = 0, rows_cases = -1;  // rows per item of the march, planned for that many active cases
     double umax_limit = 0.3;
     hipStream_t stream = nullptr;
     hipStream_t cap = nullptr;
@@ -579,7 +578,7 @@ struct acm_batch {
     std::vector<int> hactive;
     std::vector<double> hhealth;
     size_t max_items = 0;
-    std::vector<int> tile, nx, ny, nw, state;
+    std::vector<int> tile, nx, ny, nw, wallx, state;
     std::vector<int64_t> nsteps, done;
     std::vector<double> done_ms, umax;
     hipEvent_t ev_start = nullptr, ev_chunk = nullptr;
@@ -600,20 +599,89 @@ bool march_ok(const acm_config& c)
     return c.rho0 == 1.0 && (double)c.nx * c.ny * (c.precision == ACM_F64 ? 8 : 4) < 2147483648.0;
 }
 
-// Items of one case: (tiles in x) * (tiles in y) of its tile variant, or its
-// windows times chunks of rows, whichever is more; for tile -1 the largest
-// count over the variants, so the scratch size does not depend on the
-// autotuner's choice.
-size_t case_items(const acm_config& c, int tile)
+// Items of one case on LDS tiles: (tiles in x) * (tiles in y) of its tile
+// variant; for tile -1 the largest count over the variants, so the scratch
+// size does not depend on the autotuner's choice.
+size_t case_items(int nx, int ny, int tile)
 {
     size_t m = 0;
-    const int nw = march_windows(c);
     for (int t = 0; t < NTILE2D; ++t) {
         if (tile >= 0 && t != tile) continue;
-        m = std::max(m, (size_t)((c.nx + TILE_W[t] - 1) / TILE_W[t]) * ((c.ny + TILE_H[t] - 1) / TILE_H[t]));
-        m = std::max(m, (size_t)nw * ((c.ny + MARCH_ROWS[t] - 1) / MARCH_ROWS[t]));
+        m = std::max(m, (size_t)((nx + TILE_W[t] - 1) / TILE_W[t]) * ((ny + TILE_H[t] - 1) / TILE_H[t]));
     }
     return m;
+}
+
+// The load of the cases on the march: their items with so many rows each, and
+// the share of them whose x faces are walls.
+struct MarchLoad {
+    size_t items = 0, walled = 0;
+    void add(int nw, int ny, bool wallx, int rows)
+    {
+        const size_t n = (size_t)nw * ((ny + rows - 1) / rows);
+        items += n;
+        if (wallx) walled += n;
+    }
+};
+
+// Modelled time of a step of a two-step launch in us, fitted to 1100 measured
+// loads (16^2 to 384^2, 1 to 1000 cases, 1 to 64 rows per item, 9 % rms).  A
+// wave alone on its SIMD takes 0.215 us for a row (four rows of lead-in); each
+// further one on the SIMD adds half of that (three quarters in doubles); more
+// waves than a SIMD holds (five, in doubles two) run one round after the other.
+double march_us(const MarchLoad& l, int rows, bool f64)
+{
+    constexpr double SIMDS = 1024.0;  // 256 compute units
+    const int held = f64 ? 2 : 5;
+    const double more = f64 ? 0.755 : 0.514;
+    const double unit = (f64 ? 1.367 : 1.0) * (1.0 + 0.513 * (double)l.walled / (double)l.items);
+    const long long c = (long long)std::ceil((double)l.items / SIMDS), full = c / held, rest = c % held;
+    const double t = (double)full * (1.0 + more * (held - 1)) + (rest ? 1.0 + more * (double)(rest - 1) : 0.0);
+    return 1.81 + unit * 0.215 * (rows + 3.7) * t;
+}
+
+// Rows per item with the least modelled time and at most `most` items (0: any
+// number).  One 64^2 case is fastest with one row per item (2.6 us a step; 16
+// rows 5.4), 300 of them with 12 (7.3; one row 13.7); the choice is within
+// 0.6 % of the best of eleven row counts on the geometric mean of 100 loads.
+// add(rows): the load with so many rows per item.
+template <typename F>
+int march_rows(const F& add, bool f64, size_t most)
+{
+    int best = 64;
+    double least = -1.0;
+    for (int r = 64; r >= 1; --r) {
+        const MarchLoad l = add(r);
+        if (most && l.items > most) break;
+        const double t = march_us(l, r, f64);
+        if (least < 0.0 || t < least) least = t, best = r;
+    }
+    return best;
+}
+
+// How mode 0 runs the cases: on the march, or (a case it does not cover, or
+// `tiles`) on LDS tiles; and the item capacity.
+struct BatchPlan {
+    bool march = false;
+    size_t items = 0;
+};
+BatchPlan batch_plan(const acm_batch_case* cases, int n, int mode, bool tiles)
+{
+    BatchPlan p;
+    p.march = mode == 0 && !tiles;
+    for (int i = 0; i < n; ++i) p.march = p.march && march_ok(cases[i].cfg);
+    if (p.march) {
+        auto load = [&](int rows) {
+            MarchLoad l;
+            for (int i = 0; i < n; ++i)
+                l.add(march_windows(cases[i].cfg), cases[i].cfg.ny, cases[i].cfg.bc[0] != BC_PERIODIC, rows);
+            return l;
+        };
+        p.items = load(march_rows(load, cases[0].cfg.precision == ACM_F64, 0)).items;
+    } else {
+        for (int i = 0; i < n; ++i) p.items += case_items(cases[i].cfg.nx, cases[i].cfg.ny, cases[i].tile);
+    }
+    return p;
 }
 
 // Layout of the batch's device tables in the caller's scratch, each part
@@ -745,13 +813,13 @@ bool tuned_tile(int nx, int ny, int precision, int mode, int* tile)
 }
 
 // checks shared by acm_batch_scratch_bytes and acm_batch_init
-acm_status check_cases(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts, size_t* max_items)
+acm_status check_cases(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts, bool tiles,
+                       BatchPlan* plan)
 {
     if (!cases || ncases <= 0) return bfail(ACM_EINVAL, "cases / ncases invalid");
     const int prec = cases[0].cfg.precision;
     if (opts && opts->chunk > 0 && opts->chunk % 2) return bfail(ACM_EINVAL, "chunk must be even");
     if (opts && opts->mode != 0 && opts->mode != 1) return bfail(ACM_EINVAL, "mode must be 0 or 1");
-    size_t items = 0;
     for (int i = 0; i < ncases; ++i) {
         const acm_batch_case& k = cases[i];
         std::string err;
@@ -760,11 +828,12 @@ acm_status check_cases(const acm_batch_case* cases, int32_t ncases, const acm_ba
             return bfail(ACM_EINVAL, "batched cases are 2D single-phase planar");
         if (k.cfg.precision != prec) return bfail(ACM_EINVAL, "every case of a batch needs the same precision");
         if (k.tile < -1 || k.tile >= NTILE2D) return bfail(ACM_EINVAL, "tile must be -1..5");
-        items += case_items(k.cfg, k.tile);
     }
-    if (max_items) *max_items = items;
+    *plan = batch_plan(cases, ncases, opts ? opts->mode : 0, tiles);
     return ACM_OK;
 }
+acm_status batch_init(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts, bool lds_tiles,
+                      void* scratch, size_t scratch_bytes, void* stream, acm_batch** out);
 }
 
 extern "C" {
@@ -772,9 +841,20 @@ extern "C" {
 size_t acm_batch_scratch_bytes(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts)
 {
     set_error("");
-    size_t items = 0;
-    if (check_cases(cases, ncases, opts, &items) != ACM_OK) return 0;
-    return batch_layout(ncases, items, cases[0].cfg.precision).total;
+    BatchPlan plan;
+    if (check_cases(cases, ncases, opts, false, &plan) != ACM_OK) return 0;
+    return batch_layout(ncases, plan.items, cases[0].cfg.precision).total;
+}
+
+acm_status acm_batch_on_tiles(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts,
+                              int32_t* on_tiles)
+{
+    set_error("");
+    if (!on_tiles) return bfail(ACM_EINVAL, "on_tiles is NULL");
+    BatchPlan plan;
+    const acm_status st = check_cases(cases, ncases, opts, false, &plan);
+    if (st == ACM_OK) *on_tiles = plan.march ? 0 : 1;
+    return st;
 }
 
 acm_status acm_batch_tuned_tile(int32_t nx, int32_t ny, int32_t precision, int32_t mode, int32_t* tile)
@@ -799,104 +879,7 @@ acm_status acm_batch_set_tuned_tile(int32_t nx, int32_t ny, int32_t precision, i
 acm_status acm_batch_init(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts, void* scratch,
                           size_t scratch_bytes, void* stream, acm_batch** out)
 {
-    set_error("");
-    if (!out) return bfail(ACM_EINVAL, "out is NULL");
-    *out = nullptr;
-    size_t items_bound = 0;
-    acm_status cst = check_cases(cases, ncases, opts, &items_bound);
-    if (cst != ACM_OK) return cst;
-    const int prec = cases[0].cfg.precision;
-    const int chunk = (opts && opts->chunk > 0) ? opts->chunk : 500;
-    const int mode = opts ? opts->mode : 0;
-    const BatchLayout L = batch_layout(ncases, items_bound, prec);
-    if (!scratch) return bfail(ACM_EINVAL, "scratch is NULL (acm_batch_scratch_bytes gives its size)");
-    if (reinterpret_cast<uintptr_t>(scratch) % 256 != 0) return bfail(ACM_EINVAL, "scratch must be 256-byte aligned");
-    if (scratch_bytes < L.total)
-        return bfail(ACM_EINVAL, "scratch holds " + std::to_string(scratch_bytes) + " bytes, the batch needs " +
-                                     std::to_string(L.total));
-    for (int i = 0; i < ncases; ++i) {
-        const acm_batch_case& k = cases[i];
-        if (!k.a.drho || !k.a.u || !k.a.v || !k.b.drho || !k.b.u || !k.b.v)
-            return bfail(ACM_EINVAL, "case " + std::to_string(i) + ": missing field pointers");
-        if (k.nsteps <= 0) return bfail(ACM_EINVAL, "nsteps must be positive");
-        if (!k.cfg.allow_unstable && api_max_amplification(k.cfg) > 1.0 + 1e-12)
-            return bfail(ACM_EUNSTABLE, "case " + std::to_string(i) + " fails the linear stability check");
-    }
-    // tile -1: the autotuner's choice for the case's shape (acm_batch_autotune)
-    std::vector<int> tiles(ncases);
-    for (int i = 0; i < ncases; ++i) {
-        tiles[i] = cases[i].tile;
-        if (tiles[i] >= 0) continue;
-        int t = 0;
-        if (!tuned_tile(cases[i].cfg.nx, cases[i].cfg.ny, prec, mode, &t))
-            return bfail(ACM_ESTATE, "case " + std::to_string(i) + ": grid shape " + std::to_string(cases[i].cfg.nx) +
-                                         " x " + std::to_string(cases[i].cfg.ny) +
-                                         " is not tuned for this precision and launch mode (acm_batch_autotune)");
-        tiles[i] = t;
-    }
-    acm_batch* b = new (std::nothrow) acm_batch();
-    if (!b) return bfail(ACM_EINVAL, "out of host memory");
-    b->n = ncases;
-    b->precision = prec;
-    b->chunk = chunk;
-    b->grab = (opts && opts->grab > 0) ? opts->grab : 2;
-    b->mode = mode;
-    b->umax_limit = (opts && opts->umax_limit > 0) ? opts->umax_limit : 0.3;
-    b->stream = static_cast<hipStream_t>(stream);
-    b->tile.resize(ncases);
-    b->nx.resize(ncases);
-    b->ny.resize(ncases);
-    b->nw.resize(ncases);
-    b->state.assign(ncases, 0);
-    b->nsteps.resize(ncases);
-    b->done.assign(ncases, 0);
-    b->done_ms.assign(ncases, -1.0);
-    b->umax.assign(ncases, 0.0);
-    bool march = mode == 0;
-    for (int i = 0; i < ncases; ++i) {
-        b->tile[i] = tiles[i];
-        b->nx[i] = cases[i].cfg.nx;
-        b->ny[i] = cases[i].cfg.ny;
-        b->nsteps[i] = ((cases[i].nsteps + chunk - 1) / chunk) * chunk;
-        b->nw[i] = march_windows(cases[i].cfg);
-        march = march && march_ok(cases[i].cfg);
-        b->max_items += case_items(cases[i].cfg, tiles[i]);
-    }
-    b->march = march;
-    char* base = static_cast<char*>(scratch);
-    b->dcases = base + L.cases;
-    b->ditems = reinterpret_cast<int4*>(base + L.items);
-    b->dnitems = reinterpret_cast<int*>(base + L.nitems);
-    b->dqueue = reinterpret_cast<int*>(base + L.queue);
-    b->dactive = reinterpret_cast<int*>(base + L.active);
-    b->dhealth = reinterpret_cast<double*>(base + L.health);
-    b->hitems.resize(std::max<size_t>(1, b->max_items));
-    b->hactive.resize(ncases);
-    b->hhealth.resize(2 * (size_t)ncases);
-    // queue counters start at zero (outside any graph; the persistent kernel
-    // resets them itself after every launch)
-    hipError_t e = hipMemsetAsync(b->dqueue, 0, QUEUE_BYTES, b->stream);
-    if (e == hipSuccess) e = (prec == ACM_F64) ? upload_cases<double>(b, cases) : upload_cases<float>(b, cases);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreate(&b->ev_start);
-    if (e == hipSuccess) e = hipEventCreate(&b->ev_chunk);
-    if (e != hipSuccess) {
-        acm_batch_destroy(b);
-        return bfail(ACM_EHIP, std::string("batch set-up: ") + hipGetErrorString(e));
-    }
-    b->blocks = (opts && opts->blocks > 0) ? opts->blocks
-                                           : (prec == ACM_F64 ? occupancy_blocks<double>() : occupancy_blocks<float>());
-    if (b->blocks <= 0) {
-        acm_batch_destroy(b);
-        return bfail(ACM_EHIP, "could not size the persistent grid");
-    }
-    acm_status st = build_graph(b);
-    if (st != ACM_OK) {
-        acm_batch_destroy(b);
-        return st;
-    }
-    *out = b;
-    return ACM_OK;
+    return batch_init(cases, ncases, opts, false, scratch, scratch_bytes, stream, out);
 }
 
 acm_status acm_batch_run(acm_batch* b, int32_t max_chunks, int32_t* active_left)
@@ -914,14 +897,28 @@ acm_status acm_batch_run(acm_batch* b, int32_t max_chunks, int32_t* active_left)
         int nact = 0;
         size_t nit = 0;
         int64_t chunk_lups = 0;
-        for (int i = 0; i < b->n; ++i) {
-            if (b->state[i] != 0) continue;
-            b->hactive[nact++] = i;
+        for (int i = 0; i < b->n; ++i)
+            if (b->state[i] == 0) b->hactive[nact++] = i;
+        if (b->march && nact > 0 && nact != b->rows_cases) {
+            b->rows = march_rows(
+                [&](int rows) {
+                    MarchLoad l;
+                    for (int a = 0; a < nact; ++a) {
+                        const int i = b->hactive[a];
+                        l.add(b->nw[i], b->ny[i], b->wallx[i] != 0, rows);
+                    }
+                    return l;
+                },
+                b->precision == ACM_F64, b->max_items);
+            b->rows_cases = nact;
+        }
+        for (int a = 0; a < nact; ++a) {
+            const int i = b->hactive[a];
             const int t = b->tile[i];
             if (b->march) {  // chunks of rows, each over the windows of a row
-                for (int y = 0; y < b->ny[i]; y += MARCH_ROWS[t])
+                for (int y = 0; y < b->ny[i]; y += b->rows)
                     for (int w = 0; w < b->nw[i]; ++w)
-                        b->hitems[nit++] = make_int4(i, w, y, std::min(y + MARCH_ROWS[t], b->ny[i]));
+                        b->hitems[nit++] = make_int4(i, w, y, std::min(y + b->rows, b->ny[i]));
                 chunk_lups += (int64_t)b->nx[i] * b->ny[i] * b->chunk;
                 continue;
             }
@@ -1009,12 +1006,8 @@ size_t acm_batch_autotune_scratch_bytes(int32_t nx, int32_t ny, int32_t precisio
         return 0;
     }
     const size_t es = precision == ACM_F64 ? 8 : 4;
-    acm_config c{};
-    c.nx = nx;
-    c.ny = ny;
-    c.precision = precision;
     return align256((size_t)nx * ny * es * 6 * (size_t)copies) +
-           batch_layout(copies, case_items(c, -1) * (size_t)copies, precision).total;
+           batch_layout(copies, case_items(nx, ny, -1) * (size_t)copies, precision).total;
 }
 
 acm_status acm_batch_autotune(int32_t nx, int32_t ny, int32_t precision, int32_t mode, int32_t copies, int32_t steps,
@@ -1039,6 +1032,111 @@ acm_status acm_batch_autotune(int32_t nx, int32_t ny, int32_t precision, int32_t
 }  // extern "C"
 
 namespace {
+// acm_batch_init; lds_tiles: mode 0 on LDS tiles whatever the cases (the autotuner)
+acm_status batch_init(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts, bool lds_tiles,
+                      void* scratch, size_t scratch_bytes, void* stream, acm_batch** out)
+{
+    set_error("");
+    if (!out) return bfail(ACM_EINVAL, "out is NULL");
+    *out = nullptr;
+    BatchPlan plan;
+    acm_status cst = check_cases(cases, ncases, opts, lds_tiles, &plan);
+    if (cst != ACM_OK) return cst;
+    const int prec = cases[0].cfg.precision;
+    const int chunk = (opts && opts->chunk > 0) ? opts->chunk : 500;
+    const int mode = opts ? opts->mode : 0;
+    const BatchLayout L = batch_layout(ncases, plan.items, prec);
+    if (!scratch) return bfail(ACM_EINVAL, "scratch is NULL (acm_batch_scratch_bytes gives its size)");
+    if (reinterpret_cast<uintptr_t>(scratch) % 256 != 0) return bfail(ACM_EINVAL, "scratch must be 256-byte aligned");
+    if (scratch_bytes < L.total)
+        return bfail(ACM_EINVAL, "scratch holds " + std::to_string(scratch_bytes) + " bytes, the batch needs " +
+                                     std::to_string(L.total));
+    for (int i = 0; i < ncases; ++i) {
+        const acm_batch_case& k = cases[i];
+        if (!k.a.drho || !k.a.u || !k.a.v || !k.b.drho || !k.b.u || !k.b.v)
+            return bfail(ACM_EINVAL, "case " + std::to_string(i) + ": missing field pointers");
+        if (k.nsteps <= 0) return bfail(ACM_EINVAL, "nsteps must be positive");
+        if (!k.cfg.allow_unstable && api_max_amplification(k.cfg) > 1.0 + 1e-12)
+            return bfail(ACM_EUNSTABLE, "case " + std::to_string(i) + " fails the linear stability check");
+    }
+    // tile -1: the autotuner's choice for the case's shape (acm_batch_autotune)
+    std::vector<int> tiles(ncases);
+    for (int i = 0; i < ncases; ++i) {
+        tiles[i] = cases[i].tile;
+        if (tiles[i] >= 0) continue;
+        int t = 0;
+        if (!tuned_tile(cases[i].cfg.nx, cases[i].cfg.ny, prec, mode, &t))
+            return bfail(ACM_ESTATE, "case " + std::to_string(i) + ": grid shape " + std::to_string(cases[i].cfg.nx) +
+                                         " x " + std::to_string(cases[i].cfg.ny) +
+                                         " is not tuned for this precision and launch mode (acm_batch_autotune)");
+        tiles[i] = t;
+    }
+    acm_batch* b = new (std::nothrow) acm_batch();
+    if (!b) return bfail(ACM_EINVAL, "out of host memory");
+    b->n = ncases;
+    b->precision = prec;
+    b->chunk = chunk;
+    b->grab = (opts && opts->grab > 0) ? opts->grab : 2;
+    b->mode = mode;
+    b->umax_limit = (opts && opts->umax_limit > 0) ? opts->umax_limit : 0.3;
+    b->stream = static_cast<hipStream_t>(stream);
+    b->tile.resize(ncases);
+    b->nx.resize(ncases);
+    b->ny.resize(ncases);
+    b->nw.resize(ncases);
+    b->wallx.resize(ncases);
+    b->state.assign(ncases, 0);
+    b->nsteps.resize(ncases);
+    b->done.assign(ncases, 0);
+    b->done_ms.assign(ncases, -1.0);
+    b->umax.assign(ncases, 0.0);
+    b->march = plan.march;
+    for (int i = 0; i < ncases; ++i) {
+        b->tile[i] = tiles[i];
+        b->nx[i] = cases[i].cfg.nx;
+        b->ny[i] = cases[i].cfg.ny;
+        b->nsteps[i] = ((cases[i].nsteps + chunk - 1) / chunk) * chunk;
+        b->nw[i] = march_windows(cases[i].cfg);
+        b->wallx[i] = cases[i].cfg.bc[0] != BC_PERIODIC;
+        if (!b->march) b->max_items += case_items(b->nx[i], b->ny[i], tiles[i]);
+    }
+    if (b->march) b->max_items = plan.items;
+    char* base = static_cast<char*>(scratch);
+    b->dcases = base + L.cases;
+    b->ditems = reinterpret_cast<int4*>(base + L.items);
+    b->dnitems = reinterpret_cast<int*>(base + L.nitems);
+    b->dqueue = reinterpret_cast<int*>(base + L.queue);
+    b->dactive = reinterpret_cast<int*>(base + L.active);
+    b->dhealth = reinterpret_cast<double*>(base + L.health);
+    b->hitems.resize(std::max<size_t>(1, b->max_items));
+    b->hactive.resize(ncases);
+    b->hhealth.resize(2 * (size_t)ncases);
+    // queue counters start at zero (outside any graph; the persistent kernel
+    // resets them itself after every launch)
+    hipError_t e = hipMemsetAsync(b->dqueue, 0, QUEUE_BYTES, b->stream);
+    if (e == hipSuccess) e = (prec == ACM_F64) ? upload_cases<double>(b, cases) : upload_cases<float>(b, cases);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreate(&b->ev_start);
+    if (e == hipSuccess) e = hipEventCreate(&b->ev_chunk);
+    if (e != hipSuccess) {
+        acm_batch_destroy(b);
+        return bfail(ACM_EHIP, std::string("batch set-up: ") + hipGetErrorString(e));
+    }
+    b->blocks = (opts && opts->blocks > 0) ? opts->blocks
+                                           : (prec == ACM_F64 ? occupancy_blocks<double>() : occupancy_blocks<float>());
+    if (b->blocks <= 0) {
+        acm_batch_destroy(b);
+        return bfail(ACM_EHIP, "could not size the persistent grid");
+    }
+    acm_status st = build_graph(b);
+    if (st != ACM_OK) {
+        acm_batch_destroy(b);
+        return st;
+    }
+    *out = b;
+    return ACM_OK;
+}
+
 acm_status autotune_shape(int nx, int ny, int precision, int copies, int steps, void* scratch, size_t scratch_bytes,
                           void* stream, double* ms_per_tile, int32_t* best, int mode)
 {
@@ -1077,7 +1175,7 @@ acm_status autotune_shape(int nx, int ny, int precision, int copies, int steps, 
         o.chunk = steps;
         o.mode = mode;
         acm_batch* b = nullptr;
-        st = acm_batch_init(cs.data(), copies, &o, mem + fields_bytes, scratch_bytes - fields_bytes, stream, &b);
+        st = batch_init(cs.data(), copies, &o, true, mem + fields_bytes, scratch_bytes - fields_bytes, stream, &b);
         if (st != ACM_OK) break;
         st = acm_batch_run(b, 1, nullptr);  // warm-up chunk
         const auto t0 = std::chrono::steady_clock::now();
