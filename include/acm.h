@@ -296,7 +296,7 @@ typedef struct acm_batch_case_status {
 
 /* *on_tiles = 1 where acm_batch_init would run these cases on LDS tiles (mode
  * 1, or mode 0 with a case of rho0 other than 1 or of 2 GiB per field and
- * more), 0 where it would run them on the register march, which uses no tile
+ * more, or with enough grids of fewer than some 30 columns), 0 where it would run them on the register march, which uses no tile
  * variant.  Pure host call. */
 acm_status acm_batch_on_tiles(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts,
                               int32_t* on_tiles);

@@ -659,8 +659,29 @@ int march_rows(const F& add, bool f64, size_t most)
     return best;
 }
 
-// How mode 0 runs the cases: on the march, or (a case it does not cover, or
-// `tiles`) on LDS tiles; and the item capacity.
+// Grids much narrower than a window leave most lanes of the march without a
+// node.  That costs nothing while the chip is not full, but LDS tiles are ahead
+// where it is: 1000 cases of 16^2 5.2 us a step on tiles and 5.9 marched
+// (doubles 6.3 and 8.1), 2128 walled ones of 14 x 47 17.6 and 24.9 (doubles 27.8
+// and 46.0), 443 walled ones of 32^2 in doubles 9.7 and 11.6; but 300 of 33^2
+// 8.1 and 5.0, 64 of 16^2 3.8 and 2.7.  Of 900 random loads (8 to 400 columns, up
+// to 3000 cases) the march is at most 5 % behind on its side of this line.
+bool march_too_narrow(const acm_batch_case* cases, int n)
+{
+    const bool f64 = cases[0].cfg.precision == ACM_F64;
+    double nodes = 0.0, rows = 0.0, walled = 0.0;  // of the cases; window rows of the march
+    for (int i = 0; i < n; ++i) {
+        const double r = (double)march_windows(cases[i].cfg) * cases[i].cfg.ny;
+        nodes += (double)cases[i].cfg.nx * cases[i].cfg.ny;
+        rows += r;
+        if (cases[i].cfg.bc[0] != BC_PERIODIC) walled += r;
+    }
+    const double lanes = f64 ? 0.4 + 0.11 * walled / rows : 0.4;  // walls in x cost the march more in doubles
+    return nodes < lanes * 64.0 * rows && rows >= (f64 ? 1400.0 : 6000.0);
+}
+
+// How mode 0 runs the cases: on the march, or (a case it does not cover, mostly
+// empty windows, or `tiles`) on LDS tiles; and the item capacity.
 struct BatchPlan {
     bool march = false;
     size_t items = 0;
@@ -670,6 +691,7 @@ BatchPlan batch_plan(const acm_batch_case* cases, int n, int mode, bool tiles)
     BatchPlan p;
     p.march = mode == 0 && !tiles;
     for (int i = 0; i < n; ++i) p.march = p.march && march_ok(cases[i].cfg);
+    p.march = p.march && !march_too_narrow(cases, n);
     if (p.march) {
         auto load = [&](int rows) {
             MarchLoad l;

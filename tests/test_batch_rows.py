@@ -75,3 +75,25 @@ result = [l[0] for l in launches()]
 ''', tmp_path)
     steps = [n for n in names if "batch_health_kernel" not in n]
     assert steps and all("batch_grid_kernel" in n for n in steps)
+
+
+def test_narrow_grids_that_fill_the_chip_run_on_tiles(tmp_path):
+    """(nx, ny, cases, precision, on tiles): both sides of the line, as measured"""
+    loads = [(16, 16, 1000, "f32", 1), (16, 16, 1000, "f64", 1), (16, 16, 64, "f32", 0), (16, 16, 1, "f64", 0),
+             (14, 47, 2128, "f32", 1), (10, 145, 59, "f64", 1), (16, 199, 190, "f32", 1), (12, 70, 32, "f32", 0),
+             (33, 33, 300, "f32", 0), (33, 33, 300, "f64", 0), (64, 64, 300, "f32", 0), (64, 64, 300, "f64", 0)]
+    walled = [(32, 32, 443, "f64", 1), (32, 32, 443, "f32", 0), (64, 64, 300, "f64", 0)]
+    res = run(f'''
+import ctypes
+result = []
+for w, (nx, ny, n, prec, _) in [(0, l) for l in {loads}] + [(1, l) for l in {walled}]:
+    reset()
+    batch([acm.make_config(2, nx, ny, nu=0.03, precision=prec, bc=(w, w, w, w, 0, 0))] * n, [5] * n)
+    arr, opts = [k for k in keep if isinstance(k, tuple)][-1]
+    on = ctypes.c_int32()
+    acm.check(acm.lib().acm_batch_on_tiles(arr, n, ctypes.byref(opts), ctypes.byref(on)))
+    result.append([on.value, launches()[0][0]])
+''', tmp_path)
+    for (nx, ny, n, prec, want), (on_tiles, name) in zip(loads + walled, res):
+        assert on_tiles == want, (nx, ny, n, prec)
+        assert ("batch_grid_kernel" if want else "batch_march_kernel") in name
