@@ -173,9 +173,16 @@ March2d march2d_multi_plan(const Coef<T>& c, bool axi);  // the lv with the leas
 template <typename T>
 hipError_t launch_march2d(const Coef<T>& c, const State<T>& in, const State<T>& out, bool axi, const March2d& p,
                           hipStream_t s);
-// One 3D step as a register march (kern_march3d.hip)
+// One 3D step as a register march (kern_march3d.hip): launch shape (rows per
+// wave, planes per chunk) and its modelled time
+struct March3d {
+    int ry, zc;
+    double us;
+};
 bool march3d_ok(const Coef<float>& c);
-hipError_t launch_march3d(const Coef<float>& c, const State<float>& in, const State<float>& out, hipStream_t s);
+March3d march3d_plan(const Coef<float>& c);
+hipError_t launch_march3d(const Coef<float>& c, const State<float>& in, const State<float>& out, const March3d& p,
+                          hipStream_t s);
 // Two 3D steps in one launch (in -> out holds level n+2) on fully periodic
 // boxes with rho0 = 1 and fields below 2 GiB, selected by tile codes 14 and
 // 15; step3d_pair_ok says whether the configuration and tile code allow it

@@ -1,0 +1,29 @@
+"""Which kernel the 3D FP32 default takes (recorded launches, no GPU): the
+march and the column kernel on grids where each is measured ahead by a
+tenth or more."""
+from hip_record import run
+
+PER, WALL = 0, 1
+FACES = {"per": (PER,) * 6, "cav": (WALL,) * 6, "duct": (PER, PER, WALL, WALL, WALL, WALL),
+         "chz": (PER, PER, PER, PER, WALL, WALL), "wx": (WALL, WALL, PER, PER, PER, PER)}
+COLUMNS = [(14, 205, 137, "per"), (22, 113, 177, "per"), (16, 16, 800, "cav"), (16, 800, 16, "per"),
+           (17, 175, 280, "cav"), (9, 184, 114, "duct"), (10, 151, 297, "chz"), (12, 124, 319, "wx"),
+           (128, 38, 86, "cav"), (127, 90, 33, "cav"), (65, 65, 65, "cav"), (149, 181, 15, "duct"),
+           (5, 200, 200, "per"), (8, 8, 4000, "duct")]
+MARCH = [(200, 99, 70, "duct"), (100, 100, 100, "per"), (256, 100, 80, "cav"),
+         (200, 200, 160, "per"), (40, 40, 40, "per"), (40, 40, 40, "cav"), (64, 128, 128, "per"),
+         (32, 15, 30, "per")]
+
+
+def test_default_kernel(tmp_path):
+    grids = COLUMNS + MARCH
+    res = run(f'''
+result = []
+for nx, ny, nz, f in {grids}:
+    reset()
+    solver(acm.make_config(3, nx, ny, nz, nu=0.03, bc={FACES}[f], precision="f32", graph_chunk=2))
+    result.append(sorted({{l[0] for l in launches()}}))
+''', tmp_path)
+    for g, names in zip(grids, res):
+        want = "step3d_kernel" if g in COLUMNS else "march3d_kernel"
+        assert len(names) == 1 and want in names[0], (g, names)
