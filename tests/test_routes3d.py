@@ -27,3 +27,24 @@ for nx, ny, nz, f in {grids}:
     for g, names in zip(grids, res):
         want = "step3d_kernel" if g in COLUMNS else "march3d_kernel"
         assert len(names) == 1 and want in names[0], (g, names)
+
+
+LDS_2P = [(13, 161, 281, "wx"), (16, 253, 33, "per"), (9, 119, 131, "duct"), (32, 287, 113, "wx"),
+          (128, 254, 182, "chz"), (192, 205, 135, "chz")]
+MARCH_2P = [(96, 96, 96, "chz"), (32, 32, 32, "per"), (25, 20, 11, "per"), (64, 362, 274, "wx"),
+            (192, 152, 151, "duct"), (128, 78, 227, "cav"), (200, 200, 200, "per")]
+
+
+def test_default_kernel_two_phase(tmp_path):
+    grids = LDS_2P + MARCH_2P
+    res = run(f'''
+result = []
+for nx, ny, nz, f in {grids}:
+    reset()
+    cfg = acm.make_config(3, nx, ny, nz, nu=0.03, bc={FACES}[f], precision="f32", graph_chunk=2, two_phase=True,
+                          sigma=0.001, width=4.0, mobility=0.02)
+    solver(cfg)
+    result.append(sorted({{l[0] for l in launches()}}))
+''', tmp_path)
+    for g, names in zip(grids, res):
+        assert any(("stage1_kernel" if g in LDS_2P else "stage1_march_kernel") in n for n in names), (g, names)
