@@ -28,6 +28,7 @@
 // lets eight workgroups share a CU.  The default where walls have no wetting
 // rule is the register march further below.
 #include <algorithm>
+#include <cmath>
 
 #include "acm_internal.h"
 #include "kern_axisym.h"
@@ -620,6 +621,7 @@ int compute_units()
 // 2048 x 1024, 2.6 % rms).  us[w - 1]: time of one row of one wave, per wave,
 // when w waves share a SIMD; more waves than a SIMD holds run one round after
 // the other.  3.1 rows stand for the eight halo rows, which are formed in part.
+constexpr double LAUNCH_US = 2.9;
 double launch_us(int vx, int nw, int ny, int rows, bool f64, bool axi, double bytes)
 {
     static const double f32_1[4] = {0.593, 0.398, 0.369, 0.329}, f32_2[2] = {0.838, 0.618}, f64_1[2] = {0.775, 0.575};
@@ -631,7 +633,7 @@ double launch_us(int vx, int nw, int ny, int rows, bool f64, bool axi, double by
     if (whole > 2) alu *= (0.19 * nb / ncu + 0.81 * whole) / whole;
     alu *= (rows + 3.1) * (axi ? 1.05 : 1.0);
     const double mem = bytes * (1.0 + 2.0 / rows) / (bytes < 230e6 ? 8.1e6 : 5.5e6);
-    return 2.9 + std::max(alu, mem) + 0.3 * std::min(alu, mem);
+    return LAUNCH_US + std::max(alu, mem) + 0.3 * std::min(alu, mem);
 }
 
 // Launch shape: columns per lane and rows per chunk; vx = 0: not marched.
@@ -639,12 +641,23 @@ struct Plan {
     int vx, rows;
 };
 
-// The shape with the least modelled time.  Not marched: wetting walls (their
-// ghosts take a rule of their own), rho0 != 1, and in planar doubles the sizes
-// where the tile kernel's 32 x 16 tiles come to at most two per compute unit
-// and the march needs more than 10.5 us: 512 x 512 10.5 us with tiles, 11.0
-// marched, but 512 x 400 10.9 and 10.2, 560 x 512 12.7 and 11.9.
+// Modelled time in us of the tile kernel's launch (32 x 16 tiles), fitted to
+// 1800 measured grids (8 to 4000 columns, 8 to 20000 rows, 4 % rms).  n: tiles
+// per compute unit.
+double tiles_us(double n, bool f64, bool axi, bool walls)
+{
+    const double c = std::ceil(n);
+    if (axi) return f64 ? 7.5 + 0.28 * n + 2.33 * c : 7.8 + 0.21 * n + 1.19 * c;
+    return (f64 ? 5.8 + 0.45 * n + 1.81 * c : 5.9 + 0.16 * n + 1.05 * c) + (walls ? 0.75 : 0.0);
+}
 
+// The shape with the least modelled time.  Not marched: wetting walls (their
+// ghosts take a rule of their own), rho0 != 1, and grids on which the tile
+// kernel is ahead: those whose rows fill few of the lanes, and some of few
+// rows or few tiles.  us per step, tiles and march: 16 x 15602 axisymmetric
+// doubles 17.1 and 22.0, 1632 x 78 doubles 9.1 and 10.3, 1983 x 174 8.8 and 9.8,
+// 512 x 512 doubles 10.5 and 11.0; but 512 x 400 doubles 10.9 and 10.2, 1024 x
+// 1024 18.3 and 14.5.
 template <typename T>
 Plan plan(const Coef<T>& c, bool axi)
 {
@@ -661,7 +674,12 @@ Plan plan(const Coef<T>& c, bool axi)
             if (best.vx == 0 || t < least) best = Plan{vx, r}, least = t;
         }
     }
-    if (f64 && !axi && least > 10.5 && ((c.nx + 31) / 32) * ((c.ny + 15) / 16) <= 2 * compute_units()) best.vx = 0;
+    const double n = (double)((c.nx + 31) / 32) * ((c.ny + 15) / 16) / compute_units();
+    // not in the model: the x faces' selects, and what wide grids of few rows take
+    // more (7 to 14 % beyond 1300 columns)
+    double work = (least - LAUNCH_US) * (wall ? 1.16 : 1.02);
+    if (c.ny < 170 && c.nx > 800) work *= 1.0 + 0.12 * std::log2(std::min(c.nx, 1600) / 800.0);
+    if (LAUNCH_US + work > 0.97 * tiles_us(n, f64, axi, c.nonperiodic != 0)) best.vx = 0;
     return best;
 }
 
