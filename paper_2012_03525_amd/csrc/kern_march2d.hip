@@ -121,6 +121,11 @@ March2d march2d_plan(const Coef<T>& c, bool axi, int lv)
     const bool f64 = sizeof(T) == 8, wall = c.bc[0] != BC_PERIODIC;
     const double nodes = (double)c.nx * c.ny;
     if (c.rho0 != T(1) || nodes * sizeof(T) >= 2147483648.0) return best;
+    // Tall grids of rows of up to half a window stay on the axisymmetric tiles:
+    // us per step, tiles and march (two steps per launch), doubles 20 x 12320
+    // 8.6 and 10.0, 13 x 7319 5.8 and 6.5, FP32 10 x 10316 5.8 and 6.3; 12 x 4217
+    // doubles 5.7 and 5.8.  Planar ones march at 0.67 of the tiles' time.
+    if (axi && c.nx <= 32 && c.ny >= (f64 ? 4000 : 8000)) return best;
     for (int vx = 1; vx <= (f64 ? 1 : 2); vx *= 2) {
         const int nw = windows_of(vx, lv, c.nx, wall);
         if (nw == 0 || (f64 && lv == 3)) continue;

@@ -28,3 +28,26 @@ for nx, ny, f, prec in {grids}:
     for g, names in zip(grids, res):
         want = "twophase2d_kernel" if g in TILES_2P else "twophase_march_kernel"
         assert len(names) == 1 and want in names[0], (g, names)
+
+
+# single-phase: (nx, ny, faces, precision, tile kernel)
+SINGLE = [(20, 12320, "axi_wx", "f64", "axisym2d_kernel"), (13, 7319, "axi", "f64", "axisym2d_kernel"),
+          (10, 10316, "axi_wx", "f32", "axisym2d_kernel"), (13, 1000, "axi", "f64", None),
+          (48, 12320, "axi_wx", "f64", None), (20, 12320, "wx", "f64", None), (4096, 2048, "axi", "f32", None),
+          (64, 64, "per", "f64", None)]
+
+
+def test_single_phase_default_kernel(tmp_path):
+    res = run(f'''
+result = []
+for nx, ny, f, prec, _ in {SINGLE}:
+    reset()
+    h = solver(acm.make_config(2, nx, ny, nu=0.03, bc={FACES}[f], precision=prec, graph_chunk=8,
+                               axisym=f.startswith("axi")))
+    acm.check(acm.lib().acm_step(h))
+    acm.check(acm.lib().acm_run(h, 5))
+    result.append([l[0] for l in launches()])
+''', tmp_path)
+    for g, names in zip(SINGLE, res):
+        assert all((g[4] or "march2d_kernel") in n for n in names), (g, names)
+        assert g[4] is None or len(names) == 2 * 8 + 6  # one step per launch
