@@ -47,8 +47,11 @@ hipError_t launch_faces(const Coef<T>& c, const State<T>& in, const State<T>& ou
     if (axi && wx) return launch<T, VX, LV, true, true, true>(c, in, out, rows, s);
     if (axi) return launch<T, VX, LV, false, true, true>(c, in, out, rows, s);
     if (wx) return launch<T, VX, LV, true, true, false>(c, in, out, rows, s);
-    if (c.nonperiodic) return launch<T, VX, LV, false, true, false>(c, in, out, rows, s);
-    return launch<T, VX, LV, false, false, false>(c, in, out, rows, s);
+    // Two nodes per lane and two steps: without the y faces' code the compiler
+    // takes 171 registers (two waves per SIMD), with it 166 (three).
+    if constexpr (VX * LV == 4) return launch<T, VX, LV, false, true, false>(c, in, out, rows, s);
+    else if (c.nonperiodic) return launch<T, VX, LV, false, true, false>(c, in, out, rows, s);
+    else return launch<T, VX, LV, false, false, false>(c, in, out, rows, s);
 }
 
 int compute_units()
@@ -100,7 +103,9 @@ double launch_us(int vx, int lv, int nw, int ny, int rows, bool f64, bool axi, b
         work += (rows + 4 * (lv - l) + 2) * rho + (rows + 4 * (lv - l)) * mom;
     const int nb = (nw * ((ny + rows - 1) / rows) + 3) / 4, ncu = compute_units();
     const int whole = (nb + ncu - 1) / ncu;  // waves of the busiest SIMD
-    const int held = f64 ? 4 - lv : vx == 1 ? (lv == 1 ? 7 : lv == 2 ? 5 : 3) : lv == 1 ? 4 : wall ? 2 : 3;
+    // waves that a SIMD holds (registers of the compiled kernels)
+    const int held1 = lv == 1 ? 7 : lv == 3 ? 3 : axi && wall ? 4 : 5, held2 = lv == 1 ? 4 : wall ? 2 : 3;
+    const int held = f64 ? 4 - lv : vx == 1 ? held1 : held2;
     const int full = whole / held, rest = whole % held;
     double alu = full * held * ns[std::min(held, 4) - 1] + (rest ? rest * ns[std::min(rest, 4) - 1] : 0.0);
     if (whole > 2) alu *= (0.24 * nb / ncu + 0.76 * whole) / whole;  // the others take up some of its work
