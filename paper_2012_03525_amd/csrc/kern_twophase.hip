@@ -621,8 +621,9 @@ int compute_units()
 // 2048 x 1024, 2.6 % rms).  us[w - 1]: time of one row of one wave, per wave,
 // when w waves share a SIMD; more waves than a SIMD holds run one round after
 // the other.  3.1 rows stand for the eight halo rows, which are formed in part.
+// extra: factor on the rows' time.
 constexpr double LAUNCH_US = 2.9;
-double launch_us(int vx, int nw, int ny, int rows, bool f64, bool axi, double bytes)
+double launch_us(int vx, int nw, int ny, int rows, bool f64, bool axi, double bytes, double extra = 1.0)
 {
     static const double f32_1[4] = {0.593, 0.398, 0.369, 0.329}, f32_2[2] = {0.838, 0.618}, f64_1[2] = {0.775, 0.575};
     const double* us = f64 ? f64_1 : vx == 2 ? f32_2 : f32_1;
@@ -631,7 +632,7 @@ double launch_us(int vx, int nw, int ny, int rows, bool f64, bool axi, double by
     const int whole = (nb + ncu - 1) / ncu, full = whole / held, rest = whole % held;
     double alu = full * held * us[held - 1] + (rest ? rest * us[rest - 1] : 0.0);
     if (whole > 2) alu *= (0.19 * nb / ncu + 0.81 * whole) / whole;
-    alu *= (rows + 3.1) * (axi ? 1.05 : 1.0);
+    alu *= (rows + 3.1) * (axi ? 1.05 : 1.0) * extra;
     const double mem = bytes * (1.0 + 2.0 / rows) / (bytes < 230e6 ? 8.1e6 : 5.5e6);
     return LAUNCH_US + std::max(alu, mem) + 0.3 * std::min(alu, mem);
 }
@@ -677,9 +678,11 @@ Plan plan(const Coef<T>& c, bool axi)
     const double n = (double)((c.nx + 31) / 32) * ((c.ny + 15) / 16) / compute_units();
     // not in the model: the x faces' selects, and what wide grids of few rows take
     // more (7 to 14 % beyond 1300 columns)
-    double work = (least - LAUNCH_US) * (wall ? 1.16 : 1.02);
-    if (c.ny < 170 && c.nx > 800) work *= 1.0 + 0.12 * std::log2(std::min(c.nx, 1600) / 800.0);
-    if (LAUNCH_US + work > 0.97 * tiles_us(n, f64, axi, c.nonperiodic != 0)) best.vx = 0;
+    double extra = wall ? 1.16 : 1.02;
+    if (c.ny < 170 && c.nx > 800) extra *= 1.0 + 0.12 * std::log2(std::min(c.nx, 1600) / 800.0);
+    const int nw = best.vx == 2 ? march::Windows<2, 2>::count(c.nx, wall) : march::Windows<1, 2>::count(c.nx, wall);
+    const double us = launch_us(best.vx, nw, c.ny, best.rows, f64, axi, 8.0 * nodes * sizeof(T), extra);
+    if (us > 0.97 * tiles_us(n, f64, axi, c.nonperiodic != 0)) best.vx = 0;
     return best;
 }
 

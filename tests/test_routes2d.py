@@ -12,7 +12,7 @@ TILES_2P = [(16, 15602, "axi_wx", "f64"), (19, 8153, "axi_wx", "f64"), (1632, 78
             (2739, 108, "cav", "f64"), (1983, 174, "per", "f32"), (8, 30000, "cav", "f32"), (512, 512, "cav", "f64")]
 MARCH_2P = [(1024, 1024, "chan", "f32"), (1024, 1024, "chan", "f64"), (2048, 1024, "axi", "f32"),
             (2048, 1024, "axi", "f64"), (256, 256, "per", "f32"), (96, 96, "cav", "f32"), (100, 100, "cav", "f64"),
-            (512, 400, "chan", "f64")]
+            (512, 400, "chan", "f64"), (2048, 2049, "wx", "f64"), (3000, 3000, "cav", "f64")]
 
 
 def test_two_phase_default_kernel(tmp_path):
