@@ -91,10 +91,12 @@ typedef struct acm_config {
                                run ending with a one-step launch; 64x4 for
                                rho0 other than 1 and fields of 2 GiB and
                                more).  2D axisymmetric: 1 32x8, 2 64x8, 4
-                               64x4 (0: register march, else 32x16).  2D
-                               two-phase: 1 32x8, 2 64x8, 3 16x16 (0:
-                               register march where no wall has a wetting
-                               rule and rho0 = 1, else 32x16).  3D: low byte
+                               64x4 (0: register march, but on tall grids of
+                               at most 32 axial nodes and where the planar
+                               default is 64x4, 32x16).  2D two-phase: 1
+                               32x8, 2 64x8, 3 16x16 (0: register march where
+                               no wall has a wetting rule, rho0 = 1 and its
+                               modelled time is the shorter, else 32x16).  3D: low byte
                                1 32x8, 2 64x8, 3 32x4, 4 64x4, 5 64x16,
                                7 32x16, 9 128x4, 12 128x8, 13 64x8 with two
                                rows per thread on fully periodic grids
@@ -108,16 +110,19 @@ typedef struct acm_config {
                                default); 0: the whole-row kernel with 4-row
                                bands where it applies (chunk chosen for the
                                CU count; not rows of 64 nodes on 8192 of
-                               them and more), else for FP32 grids whose two sets
-                               fit 256 MB a register march along z, else 13
-                               with 64-plane chunks,
+                               them and more), else for FP32 grids whose two
+                               sets fit 256 MB a register march along z
+                               where its modelled time is the shorter, else
+                               13 with 64-plane chunks,
                                or a smaller shape and chunk (down to 32x8
                                with 4-plane chunks) when that gives fewer
                                than two workgroups per CU (FP64 accepts 3,
                                4, else 32x8); bits 8+ = z chunk / 16 (0:
                                64 planes).  3D two-phase: the flow step's
                                shape; 0 (FP32, no wetting rule on the x
-                               faces, rho0 = 1, up to 9 million nodes):
+                               faces, rho0 = 1, up to 9 million nodes, not
+                               many rows of at most 32 nodes, nor rows of
+                               128 or 192 on 260 MB of fields and more):
                                register marches along z, two launches a
                                step.  Results do not depend on the tile. */
     double wet_cos[6];      /* two-phase: cos(contact angle) of each wall face
@@ -296,8 +301,9 @@ typedef struct acm_batch_case_status {
 
 /* *on_tiles = 1 where acm_batch_init would run these cases on LDS tiles (mode
  * 1, or mode 0 with a case of rho0 other than 1 or of 2 GiB per field and
- * more, or with enough grids of fewer than some 30 columns), 0 where it would run them on the register march, which uses no tile
- * variant.  Pure host call. */
+ * more, or with enough grids of fewer than some 30 columns), 0 where it
+ * would run them on the register march, which uses no tile variant.  Pure
+ * host call. */
 acm_status acm_batch_on_tiles(const acm_batch_case* cases, int32_t ncases, const acm_batch_opts* opts,
                               int32_t* on_tiles);
 

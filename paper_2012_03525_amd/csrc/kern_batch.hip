@@ -5,20 +5,21 @@
 // active count exit at once, and the hardware dispatcher keeps as many items
 // in flight as occupancy allows.  An item is a window of columns and a chunk
 // of rows of a case, advanced two steps per launch by the register march
-// (march2d.h); a batch with a case the march does not cover (rho0 other than
-// 1) runs on LDS tiles, one workgroup per (case, tile) and step.  Mode 1: a persistent grid (CUs x occupancy
-// workgroups) pops ranges of `grab` items from an atomic counter, one range
-// ahead, and loads the next item's fields into registers while it computes
-// the current one, so its own load latency overlaps its arithmetic; the tile
-// shape is a run-time value there, so one loop serves every case.  The last
-// workgroup to finish resets the counter for the next launch.  Both modes
-// apply the node updates of the single-case kernel (tile2d.h) to the same
-// staged values, so each case's result is bitwise equal to running it
-// alone.  A
-// chunk of steps is captured once as a HIP graph (the item table and its
-// length live in device memory, so the graph survives changes of the active
-// set); after each chunk a health kernel reduces max|u| and a non-finite
-// flag per case, and the host retires finished or diverged cases.
+// (march2d.h); the rows follow from the load of the active cases.  A batch
+// with a case the march does not cover (rho0 other than 1), or of many grids
+// much narrower than a window, runs on LDS tiles, one workgroup per (case,
+// tile) and step.  Mode 1: a persistent grid (CUs x occupancy workgroups)
+// pops ranges of `grab` items from an atomic counter, one range ahead, and
+// loads the next item's fields into registers while it computes the current
+// one, so its own load latency overlaps its arithmetic; the tile shape is a
+// run-time value there, so one loop serves every case.  The last workgroup to
+// finish resets the counter for the next launch.  Both modes apply the node
+// updates of the single-case kernel (tile2d.h) to the same staged values, so
+// each case's result is bitwise equal to running it alone.  A chunk of steps
+// is captured once as a HIP graph (the item table and its length live in
+// device memory, so the graph survives changes of the active set); after each
+// chunk a health kernel reduces max|u| and a non-finite flag per case, and the
+// host retires finished or diverged cases.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -451,7 +452,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 // Mode 0, register march: one wave per active item (case, window, first
 // row, row after the last), LV steps, in windows of 64 columns; the rows of an
 // item follow from the load (march_rows).  The windows are those of two steps
-// for either LV.  Five waves per SIMD (96 VGPRs): 128-column windows take
+// for either LV.  Five waves per SIMD (96 VGPRs; at that cap two steps in FP32
+// spill one VGPR and ten SGPRs, 8 bytes of scratch): 128-column windows take
 // fewer instructions per node but 176 VGPRs, and ran the 512-case sweep at 75
 // us per step against 54; one workgroup per (case, LDS tile) took 93.
 constexpr int MARCH_LV = 2;

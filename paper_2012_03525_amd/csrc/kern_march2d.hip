@@ -1,12 +1,13 @@
 // 2D single-phase launches of the register march (march2d.h): planar and
 // axisymmetric, one to three steps per launch.
 //
-// Measured per step against the LDS tile kernels (FP32, runs of 100 steps):
-// 1024^2 periodic 8.8 -> 5.9 us (two steps per launch), 4096 x 2048
-// axisymmetric pipe 50.5 -> 31 us (a copy of the state takes 23.6), 401 x 257
-// cavity 4.2 -> 3.6 us; 64^2 FP64 3.8 -> 2.4 us.  The march is bound by instruction issue (about 65 VALU
-// instructions per node and step, 100 axisymmetric) and, on small grids, by
-// the 1.7 us of a launch inside a graph and the serial rows of a chunk.
+// Measured per step against the LDS tile kernels (FP32, runs of 100 steps, two
+// steps per launch): 1024^2 periodic 8.8 -> 5.9 us, 4096 x 2048 axisymmetric
+// pipe 50.5 -> 31 us (a copy of the state takes 23.6), 401 x 257 cavity 4.2 ->
+// 3.6 us; 64^2 FP64 3.8 -> 2.4 us.  The march is bound by instruction issue
+// (about 65 VALU instructions per node and step, 100 axisymmetric) and, on
+// small grids, by the 1.7 us of a launch inside a graph and the serial rows of
+// a chunk.
 #include <algorithm>
 
 #include "acm_internal.h"

@@ -40,7 +40,7 @@ namespace march {
 
 // rows fetched ahead: a row of 128 columns and two levels takes over a
 // microsecond, so one is enough there, and with it the kernel fits three waves
-// per SIMD
+// per SIMD (two where x faces are walls)
 constexpr int rows_ahead(int vx, int lv) { return vx * lv >= 4 ? 1 : 2; }
 
 // Windows of one row of nx nodes: 64 VX columns each, HL lanes of halo
