@@ -490,7 +490,7 @@ static hipError_t launch3d_variant(const Coef<T>& c, const State<T>& in, const S
 // 51.8 us against 32 x 4 columns with 16-plane chunks.
 struct Launch3 {
     int code, zc;
-    double per_cu;  // workgroups per compute unit
+    double per_cu, full;  // workgroups per compute unit, and their nodes as full workgroups
 };
 static Launch3 small_grid_shape(int nx, int ny, int nz, bool fp64)
 {
@@ -512,22 +512,24 @@ static Launch3 small_grid_shape(int nx, int ny, int nz, bool fp64)
     for (int i = 0; i < nc; ++i) {
         const long nb = (long)((nx + cs[i].tx - 1) / cs[i].tx) * ((ny + cs[i].ty - 1) / cs[i].ty) *
                         ((nz + cs[i].zc - 1) / cs[i].zc);
-        if (nb >= 2L * ncu || i == nc - 1) return {cs[i].code, cs[i].zc, (double)nb / ncu};
+        if (nb >= 2L * ncu || i == nc - 1)
+            return {cs[i].code, cs[i].zc, (double)nb / ncu,
+                    (double)nx * ny * nz / ((double)cs[i].tx * cs[i].ty * cs[i].zc * ncu)};
     }
-    return {0, 64, 1.0};
+    return {0, 64, 1.0, 1.0};
 }
 
-// Modelled time in us of the FP32 column launch of that shape, fitted to 640
-// random grids (8 to 320 nodes a side up to 256 MB of state, 5 % rms with
-// walls, 7 % without): planes of a chunk times the workgroups that a compute
-// unit takes, partly together.
+// Modelled time in us of the FP32 column launch of that shape, fitted to 2900
+// random grids (8 to 320 nodes a side up to 256 MB of state, 4 % rms with
+// walls, 5 % without): planes of a chunk times the workgroups that a compute
+// unit takes, partly together; full ones share its caches.
 static double column3d_us(const Coef<float>& c, const Launch3& d)
 {
-    const double planes = std::min(d.zc, c.nz), n = d.per_cu, whole = std::ceil(n);
+    const double planes = std::min(d.zc, c.nz), n = d.per_cu, whole = std::ceil(n), shared = d.full * d.full;
     const bool wide = d.code != 1;  // 64 columns
     if (c.nonperiodic)
-        return 9.9 + (wide ? 1.86 : 1.0) * (planes - 2.1) * std::max(0.0, 0.333 * n + 0.568 * whole - 0.66);
-    return 7.1 + (wide ? 1.68 : 1.0) * (planes - 2.0) * std::max(0.0, 0.478 * n + 0.364 * whole - 0.18);
+        return 7.95 + (wide ? 1.86 : 1.0) * (planes - 0.95) * (0.27 + 0.128 * n + 0.349 * whole + 0.059 * shared);
+    return 5.15 + (wide ? 1.77 : 1.0) * (planes - 0.37) * (0.393 + 0.094 * n + 0.305 * whole + 0.084 * shared);
 }
 
 // Chunk length of the default whole-row launch (6-wave, 4-row bands): the
@@ -576,8 +578,8 @@ hipError_t launch_step3d(const Coef<T>& c, const State<T>& in, const State<T>& o
     // that leave it few waves.  us per step, columns and march: 14 x 205 x 137
     // periodic 13.4 and 20.4, 128 x 38 x 86 cavity 11.9 and 15.5, 65^3 cavity
     // 12.9 and 15.5; but 256 x 100 x 80 cavity 34.4 and 28.6, 200 x 99 x 70 duct
-    // 26.7 and 19.9.  Of 700 grids drawn after the models were fitted 7 are slower than
-    // the columns by more than 3 %, the worst by 14 %.
+    // 26.7 and 19.9.  Of 700 grids drawn after the models were fitted 19 are slower than
+    // the columns by more than 3 %, the worst by 13 %.
     if constexpr (sizeof(T) == 4) {
         if (tile == 0 && march3d_ok(c)) {
             const March3d p = march3d_plan(c);

@@ -539,15 +539,17 @@ __global__ __launch_bounds__(256) void flow_stage2_march_kernel(Coef<float> c, S
 // Not marched either, being slower than the LDS kernels: rows of up to half a
 // window on launches of many waves (13 x 161 x 281 slab 58 us with the LDS
 // kernels, 70 marched, 16 x 253 x 33 periodic 30 and 35; with few waves the march
-// is ahead: 13 x 10 x 51 24 and 15), and rows of whole 64-column tiles that fill
-// at most three quarters of the windows, once the fields no longer fit the
-// cache (128 x 254 x 182, 331 MB, 190 and 219; 192 x 205 x 135, 297 MB, 174 and
-// 189; but 192 x 152 x 151, 246 MB, 155 and 136).
+// is ahead: 13 x 10 x 51 24 and 15, and on larger grids again: 18 x 258 x 242 106
+// and 90), and rows of whole 64-column tiles that fill at most three quarters
+// of the windows, once the fields no longer fit the cache (128 x 254 x 182, 331
+// MB, 190 and 219; 192 x 205 x 135, 297 MB, 174 and 189; but 192 x 152 x 151, 246
+// MB, 155 and 136).
 bool march_ok(const Coef<float>& c)
 {
     const double bytes = 56.0 * c.nx * c.ny * c.nz;
     const int nw = march::Windows<1, 1>::count(c.nx, c.bc[0] != BC_PERIODIC);
-    const bool narrow = c.nx <= 32 && (double)((c.ny + RY - 1) / RY) * c.nz >= 2500.0;
+    const double rows = (double)((c.ny + RY - 1) / RY) * c.nz;  // bands times planes
+    const bool narrow = c.nx <= 32 && rows >= 2500.0 && rows < 28000.0;
     const bool gaps = c.nx % 64 == 0 && c.nx <= 48 * nw && bytes > 260e6;
     return c.wb[0] == 0.f && c.wb[1] == 0.f && c.rho0 == 1.f && c.ny >= 2 && c.nz >= 2 && bytes <= 512e6 && !narrow &&
            !gaps;

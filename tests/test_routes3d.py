@@ -31,7 +31,7 @@ for nx, ny, nz, f in {grids}:
 
 LDS_2P = [(13, 161, 281, "wx"), (16, 253, 33, "per"), (9, 119, 131, "duct"), (32, 287, 113, "wx"),
           (128, 254, 182, "chz"), (192, 205, 135, "chz")]
-MARCH_2P = [(96, 96, 96, "chz"), (32, 32, 32, "per"), (25, 20, 11, "per"), (64, 362, 274, "wx"),
+MARCH_2P = [(18, 258, 242, "wx"), (28, 315, 260, "wx"), (96, 96, 96, "chz"), (32, 32, 32, "per"), (25, 20, 11, "per"), (64, 362, 274, "wx"),
             (192, 152, 151, "duct"), (128, 78, 227, "cav"), (200, 200, 200, "per")]
 
 
